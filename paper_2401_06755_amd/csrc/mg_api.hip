@@ -151,104 +151,6 @@ int validate(const nn4mg_config *c)
     return NN4MG_OK;
 }
 
-// ---------------------------------------------------------------- host operator
-// Link form of Eq. (k-T): (A x)_i = sum_{s in edges, corners} c_s (k_i + k_s)(x_i - x_s)
-// with c_edge = h/12, c_corner = h/24; k == NULL: the constant-coefficient filter.
-int hfold(int i, int n, int lo, int hi, int &s)
-{
-    if (i < 0) {
-        if (lo == BC_P) return i + n;
-        if (lo == BC_D) s = -s;
-        return -1 - i;
-    }
-    if (i >= n) {
-        if (hi == BC_P) return i - n;
-        if (hi == BC_D) s = -s;
-        return 2 * n - 1 - i;
-    }
-    return i;
-}
-
-void host_apply(int nx, int ny, int nz, double h, const int bc[6], const double *k, const double *x, double *y)
-{
-    for (int kk = 0; kk < nz; ++kk)
-        for (int j = 0; j < ny; ++j)
-            for (int i = 0; i < nx; ++i) {
-                const size_t c = (size_t)i + (size_t)nx * (j + (size_t)ny * kk);
-                double acc = 0.0;
-                for (int dz = -1; dz <= 1; ++dz)
-                    for (int dy = -1; dy <= 1; ++dy)
-                        for (int dx = -1; dx <= 1; ++dx) {
-                            const int m = std::abs(dx) + std::abs(dy) + std::abs(dz);
-                            if (m < 2) continue;
-                            const double cs = (m == 2) ? h / 12.0 : h / 24.0;
-                            int s = 1;
-                            const int fi = hfold(i + dx, nx, bc[0], bc[1], s);
-                            const int fj = hfold(j + dy, ny, bc[2], bc[3], s);
-                            const int fk = hfold(kk + dz, nz, bc[4], bc[5], s);
-                            const size_t q = (size_t)fi + (size_t)nx * (fj + (size_t)ny * fk);
-                            const double kl = k ? 0.5 * (k[c] + k[q]) : 1.0;
-                            acc += 2.0 * cs * kl * (x[c] - s * x[q]);
-                        }
-                y[c] = acc;
-            }
-}
-
-// Dense coarsest matrix, rank-one shift if singular, Cholesky, explicit inverse.
-int coarse_inverse(int nx, int ny, int nz, double h, const int bc[6], const double *k, int singular,
-                   std::vector<double> &inv)
-{
-    const int n = nx * ny * nz;
-    std::vector<double> A((size_t)n * n), e(n, 0.0), col(n);
-    for (int j = 0; j < n; ++j) {
-        e[j] = 1.0;
-        host_apply(nx, ny, nz, h, bc, k, e.data(), col.data());
-        for (int i = 0; i < n; ++i) A[(size_t)i * n + j] = col[i];
-        e[j] = 0.0;
-    }
-    if (singular) {
-        double cbar = 0.0;
-        for (int i = 0; i < n; ++i) cbar += A[(size_t)i * n + i];
-        cbar /= n;
-        for (auto &v : A) v += cbar / n;
-    }
-    // Cholesky A = L L^T (lower, in place)
-    for (int j = 0; j < n; ++j) {
-        double s = A[(size_t)j * n + j];
-        for (int p = 0; p < j; ++p) s -= A[(size_t)j * n + p] * A[(size_t)j * n + p];
-        if (!(s > 0.0)) return fail(NN4MG_EINVAL, "coarsest matrix is not positive definite");
-        const double d = std::sqrt(s);
-        A[(size_t)j * n + j] = d;
-        for (int i = j + 1; i < n; ++i) {
-            double t = A[(size_t)i * n + j];
-            for (int p = 0; p < j; ++p) t -= A[(size_t)i * n + p] * A[(size_t)j * n + p];
-            A[(size_t)i * n + j] = t / d;
-        }
-    }
-    inv.assign((size_t)n * n, 0.0);
-    std::vector<double> y(n);
-    for (int c = 0; c < n; ++c) {
-        for (int i = 0; i < n; ++i) {
-            double s = (i == c) ? 1.0 : 0.0;
-            for (int p = 0; p < i; ++p) s -= A[(size_t)i * n + p] * y[p];
-            y[i] = s / A[(size_t)i * n + i];
-        }
-        for (int i = n - 1; i >= 0; --i) {
-            double s = y[i];
-            for (int p = i + 1; p < n; ++p) s -= A[(size_t)p * n + i] * y[p];
-            y[i] = s / A[(size_t)i * n + i];
-        }
-        for (int i = 0; i < n; ++i) inv[(size_t)c * n + i] = y[i];
-    }
-    // symmetrise (the kernel reads column i as row i)
-    for (int i = 0; i < n; ++i)
-        for (int j = i + 1; j < n; ++j) {
-            const double v = 0.5 * (inv[(size_t)i * n + j] + inv[(size_t)j * n + i]);
-            inv[(size_t)i * n + j] = inv[(size_t)j * n + i] = v;
-        }
-    return NN4MG_OK;
-}
-
 }  // namespace
 
 struct nn4mg_hier {
@@ -405,7 +307,7 @@ size_t bytes_for(const nn4mg_config *c)
         }
     }
     const size_t nc = (size_t)(c->nx >> (L - 1)) * (c->ny >> (L - 1)) * (c->nz >> (L - 1));
-    b += 8 * nc * nc + sizeof(SolveState) + 8 * maxblk + 64 + 4;
+    b += 8 * nc * nc + sizeof(SolveState) + 8 * maxblk + 64 + 4 * kCoefFlags;
     b += kArenaAlign * (size_t)(5 * L + 12);  // alignment of each field in the arena
     if (c->outer == NN4MG_OUTER_FCG) b += 4 * 8 * (size_t)c->nx * c->ny * c->nz + 8 * (size_t)fcg_partials_needed();
     return b;
@@ -471,40 +373,60 @@ int enqueue_coef_kernels(nn4mg_hier *H)
     return NN4MG_OK;
 }
 
-int rebuild_coefficients(nn4mg_hier *H)
+// Everything derived from the coefficient in lv[0].k, the coarsest inverse
+// included.
+int enqueue_coefficients(nn4mg_hier *H)
 {
-    hipStream_t s = H->stream;
-    const nn4mg_config &c = H->cfg;
-    const bool nodal = c.coef_mode == NN4MG_COEF_NODAL;
-    int rc0 = enqueue_coef_kernels(H);
-    if (rc0) return rc0;
-    const Level &C = H->lv[H->L - 1];
-    std::vector<double> hk;
-    if (nodal) {
-        hk.resize(C.n);
-        HIP_TRY(hipMemcpyAsync(hk.data(), C.k, C.n * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-    }
-    std::vector<double> inv;
-    int rc = coarse_inverse(C.nx, C.ny, C.nz, C.h, c.bc, nodal ? hk.data() : nullptr, H->singular, inv);
+    const int rc = enqueue_coef_kernels(H);
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(H->ainv, inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    const Level &C = H->lv[H->L - 1];
+    CoarseArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.nx = C.nx;
+    a.ny = C.ny;
+    a.nz = C.nz;
+    a.n = H->nc;
+    a.h = C.h;
+    for (int f = 0; f < 6; ++f) a.bc[f] = H->cfg.bc[f];
+    a.singular = H->singular;
+    a.k = H->cfg.coef_mode == NN4MG_COEF_NODAL ? C.k : nullptr;
+    a.ainv = H->ainv;
+    a.flag = H->flag;
+    HIP_TRY(launch_coarse_inverse(a, H->stream));
     return NN4MG_OK;
 }
 
-int load_k(nn4mg_hier *H, const double *k_dev)
+int coef_status(const int *bad)
+{
+    if (bad[0]) return fail(NN4MG_EINVAL, "coefficient k must be positive and finite");
+    if (bad[1]) return fail(NN4MG_EINVAL, "coarsest matrix is not positive definite");
+    return NN4MG_OK;
+}
+
+// The coefficient set-up from k_dev (NULL: constant) and the copy of its
+// check flags to host memory, enqueued.
+int enqueue_set_coef(nn4mg_hier *H, const double *k_dev, int *bad)
 {
     hipStream_t s = H->stream;
     Level &F = H->lv[0];
-    HIP_TRY(hipMemcpyAsync(F.k, k_dev, F.n * sizeof(double), hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipMemsetAsync(H->flag, 0, sizeof(int), s));
-    HIP_TRY(launch_check_positive(F.k, F.n, H->flag, s));
-    int bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, H->flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (bad) return fail(NN4MG_EINVAL, "coefficient k must be positive and finite");
-    return rebuild_coefficients(H);
+    HIP_TRY(hipMemsetAsync(H->flag, 0, kCoefFlags * sizeof(int), s));
+    if (k_dev) {
+        HIP_TRY(hipMemcpyAsync(F.k, k_dev, F.n * sizeof(double), hipMemcpyDeviceToDevice, s));
+        HIP_TRY(launch_check_positive(F.k, F.n, H->flag, s));
+    }
+    const int rc = enqueue_coefficients(H);
+    if (rc) return rc;
+    HIP_TRY(hipMemcpyAsync(bad, H->flag, kCoefFlags * sizeof(int), hipMemcpyDeviceToHost, s));
+    return NN4MG_OK;
+}
+
+// The same, waited for: one host round trip whatever the coarsest level's size.
+int set_coef(nn4mg_hier *H, const double *k_dev)
+{
+    int bad[kCoefFlags] = {0, 0};
+    const int rc = enqueue_set_coef(H, k_dev, bad);
+    HIP_TRY(hipStreamSynchronize(H->stream));  // also on failure: the copy ends in this frame
+    return rc ? rc : coef_status(bad);
 }
 
 constexpr size_t kProfMax = 3 * 4096;
@@ -1050,7 +972,7 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
     TRY(dalloc(H, &H->partials, (size_t)maxblk));
     H->max_partials = maxblk;
     TRY(dalloc(H, &H->scal, 8));
-    TRY(dalloc(H, &H->flag, 1));
+    TRY(dalloc(H, &H->flag, kCoefFlags));
     if (cfg->outer == NN4MG_OUTER_FCG) {
         TRY(dalloc(H, &H->fcg, 4 * H->lv[0].n));
         TRY(dalloc(H, &H->fcg_part, (size_t)fcg_partials_needed()));
@@ -1066,10 +988,7 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         return fail(NN4MG_ENOMEM, "pinned host allocation failed");
     }
     if (!group) {
-        if (nodal)
-            TRY(load_k(H, k_dev));
-        else
-            TRY(rebuild_coefficients(H));
+        TRY(set_coef(H, nodal ? k_dev : nullptr));
     }
 #undef TRY
     *out = H;
@@ -1083,7 +1002,7 @@ int nn4mg_update_coef(nn4mg_t H, const double *k_dev)
     if (!H) return fail(NN4MG_EINVAL, "handle is NULL");
     if (H->cfg.coef_mode != NN4MG_COEF_NODAL) return fail(NN4MG_EINVAL, "handle has a constant coefficient");
     if (!k_dev) return fail(NN4MG_EINVAL, "k is NULL");
-    return load_k(H, k_dev);
+    return set_coef(H, k_dev);
 }
 
 int nn4mg_levels(nn4mg_t H, int *levels, int *dims, int max_levels)
@@ -1622,9 +1541,9 @@ int hier_load_coef(nn4mg_hier *H, const double *k_dev)
 {
     if (H->cfg.coef_mode == NN4MG_COEF_NODAL) {
         if (!k_dev) return fail(NN4MG_EINVAL, "nodal coefficient requires k");
-        return load_k(H, k_dev);
+        return set_coef(H, k_dev);
     }
-    return rebuild_coefficients(H);
+    return set_coef(H, nullptr);
 }
 
 // The batched cycle over copies 0 .. k - 1, captured once per k.
@@ -1683,34 +1602,9 @@ int hier_mark_idle(nn4mg_hier *H)
     return NN4MG_OK;
 }
 
-int hier_coarse_cells(const nn4mg_hier *H) { return H->nc; }
+int coef_begin(nn4mg_hier *H, const double *k_dev, int *bad) { return enqueue_set_coef(H, k_dev, bad); }
 
-int coef_begin(nn4mg_hier *H, const double *k_dev, double *hk, int *bad)
-{
-    hipStream_t s = H->stream;
-    const Level &F = H->lv[0];
-    const Level &C = H->lv[H->L - 1];
-    HIP_TRY(hipMemcpyAsync(F.k, k_dev, F.n * sizeof(double), hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipMemsetAsync(H->flag, 0, sizeof(int), s));
-    HIP_TRY(launch_check_positive(F.k, F.n, H->flag, s));
-    HIP_TRY(hipMemcpyAsync(bad, H->flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    const int rc = enqueue_coef_kernels(H);
-    if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(hk, C.k, C.n * sizeof(double), hipMemcpyDeviceToHost, s));
-    return NN4MG_OK;
-}
-
-int coef_end(nn4mg_hier *H, const double *hk, const int *bad, double *inv)
-{
-    if (*bad) return fail(NN4MG_EINVAL, "coefficient k must be positive and finite");
-    const Level &C = H->lv[H->L - 1];
-    std::vector<double> v;
-    const int rc = coarse_inverse(C.nx, C.ny, C.nz, C.h, H->cfg.bc, hk, H->singular, v);
-    if (rc) return rc;
-    std::memcpy(inv, v.data(), v.size() * sizeof(double));
-    HIP_TRY(hipMemcpyAsync(H->ainv, inv, v.size() * sizeof(double), hipMemcpyHostToDevice, H->stream));
-    return NN4MG_OK;
-}
+int coef_end(const int *bad) { return coef_status(bad); }
 
 int solve_finish_enqueue(nn4mg_hier *H, double *x)
 {

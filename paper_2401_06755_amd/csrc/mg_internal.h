@@ -213,17 +213,16 @@ double *hier_xw(nn4mg_hier *H);
 int hier_load_coef(nn4mg_hier *H, const double *k_dev);
 // Asynchronous halves of the nodal coefficient set-up and of a solve's end
 // (no host wait; the caller waits for the enqueued work in between).
-// coef_begin: copy of k, its positivity check (flag into *bad, pinned), the
-// coarse levels' coefficients and the coarsest level's k into hk (pinned,
-// hier_coarse_cells doubles); coef_end (after those arrived): the flag, the
-// coarsest inverse formed on the host into inv (pinned, cells^2 doubles) and
-// its upload.  solve_finish_enqueue (the header in host memory says the solve
+// coef_begin: copy of k, its positivity check, everything derived from k (the
+// coarse levels' coefficients, the coarsest inverse) and the copy of the two
+// check flags into bad (pinned, kCoefFlags ints); coef_end (after they
+// arrived): the status.  solve_finish_enqueue (the header in host memory says the solve
 // is over): the iterate's projection or zero fill and the copy of the whole
 // state to host memory; solve_finish_complete (after it arrived): info and
 // status, as solve_finish.
-int hier_coarse_cells(const nn4mg_hier *H);
-int coef_begin(nn4mg_hier *H, const double *k_dev, double *hk, int *bad);
-int coef_end(nn4mg_hier *H, const double *hk, const int *bad, double *inv);
+constexpr int kCoefFlags = 2;  // k not positive and finite; coarsest matrix not positive definite
+int coef_begin(nn4mg_hier *H, const double *k_dev, int *bad);
+int coef_end(const int *bad);
 int solve_finish_enqueue(nn4mg_hier *H, double *x);
 int solve_finish_complete(nn4mg_hier *H, nn4mg_info *info);
 int hier_mark_idle(nn4mg_hier *H);
@@ -265,6 +264,18 @@ hipError_t launch_sweep2(int T_is_f64, int kt, int in_mode, int out_mode, const 
 // planes, not their bytes, sets the time.
 int block2_blocks(int nx, int ny, int nz);
 hipError_t launch_sweep2_block(int T_is_f64, int kt, int out_mode, const StencilArgs &a, hipStream_t s);
+
+// ---- the coarsest level's FP64 inverse (mg_coarse.hip) ----
+struct CoarseArgs {
+    int nx, ny, nz, n;  // n = nx ny nz <= 512
+    double h;
+    int bc[6];
+    int singular;
+    const double *k;  // NULL for a constant coefficient
+    double *ainv;     // out: n x n (also the working matrix)
+    int *flag;        // flag[1] = 1 if the matrix is not positive definite
+};
+hipError_t launch_coarse_inverse(const CoarseArgs &a, hipStream_t s);
 
 // ---- coarse end of the cycle in one workgroup (mg_tail.hip) ----
 constexpr int kTailMaxLevels = 8;

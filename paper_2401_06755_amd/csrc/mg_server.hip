@@ -59,7 +59,7 @@ struct Resident {
 
 // One copy of a group: the request it runs, its view and where its request is
 // in its life: FREE; ADMIT (coefficient set-up in flight on the admission
-// stream, then the host forms the coarsest inverse); RUNNING (in the batches);
+// stream); RUNNING (in the batches);
 // FINISH (projection and state copy-back in flight on the group stream).
 enum MemberState { M_FREE = 0, M_ADMIT = 1, M_RUNNING = 2, M_FINISH = 3 };
 
@@ -70,9 +70,7 @@ struct Member {
     double t_start = 0.0;
     nn4mg_hier *V = nullptr;
     hipEvent_t ev = nullptr;  // completion of the member's ADMIT or FINISH work
-    double *hk = nullptr;     // pinned: the coarsest level's k, the inverse, the check flag
-    double *inv = nullptr;
-    int *bad = nullptr;
+    int *bad = nullptr;       // pinned: the coefficient's check flags
 };
 
 struct Group {
@@ -400,17 +398,12 @@ Group *create_group(nn4mg_server *S, const nn4mg_config &cfg)
         if (rc == NN4MG_EINVAL) S->unbatchable.push_back(cfg);
         return nullptr;
     }
-    const size_t nc = (size_t)hier_coarse_cells(g->G);
-    const size_t per_member = nc + nc * nc + 1;  // doubles: hk, inv, flag
-    bool ok = hipHostMalloc(&g->pinned, per_member * sizeof(double) * cap, hipHostMallocDefault) == hipSuccess;
+    bool ok = hipHostMalloc(&g->pinned, kCoefFlags * sizeof(int) * cap, hipHostMallocDefault) == hipSuccess;
     g->m.resize(cap);
     const bool nodal = cfg.coef_mode == NN4MG_COEF_NODAL;
     for (int c = 0; ok && c < cap; ++c) {
         Member &mb = g->m[c];
-        double *base = (double *)g->pinned + per_member * c;
-        mb.hk = base;
-        mb.inv = base + nc;
-        mb.bad = (int *)(base + nc + nc * nc);
+        mb.bad = (int *)g->pinned + kCoefFlags * c;
         ok = view_create(g->G, c, &mb.V) == NN4MG_OK &&
              hipEventCreateWithFlags(&mb.ev, hipEventDisableTiming) == hipSuccess && hier_mark_idle(mb.V) == NN4MG_OK &&
              // a constant coefficient is the same for every request: set up once
@@ -431,8 +424,8 @@ Group *create_group(nn4mg_server *S, const nn4mg_config &cfg)
 
 // Start request q on idle copy i.  The copy's stopping flag is set, so a
 // batch in flight on the group stream does not touch it: its right-hand
-// side, iterate and coefficient go in on the admission stream; the host
-// finishes the coefficient set-up when that work has arrived (advance_member).
+// side, iterate and coefficient (with all that derives from it) go in on the
+// admission stream; advance_member takes over when that work has arrived.
 void admit_member(nn4mg_server *S, Group *g, int i, const Request &q, double t_start)
 {
     Member &mb = g->m[i];
@@ -447,15 +440,15 @@ void admit_member(nn4mg_server *S, Group *g, int i, const Request &q, double t_s
     if (hipMemcpyAsync(hier_bw(V), q.b, bytes, hipMemcpyDeviceToDevice, g->admit) != hipSuccess ||
         hipMemcpyAsync(hier_xw(V), q.x, bytes, hipMemcpyDeviceToDevice, g->admit) != hipSuccess)
         rc = NN4MG_EDEVICE;
-    if (!rc && q.cfg.coef_mode == NN4MG_COEF_NODAL) rc = coef_begin(V, q.k, mb.hk, mb.bad);
+    if (!rc && q.cfg.coef_mode == NN4MG_COEF_NODAL) rc = coef_begin(V, q.k, mb.bad);
     if (!rc && hipEventRecord(mb.ev, g->admit) != hipSuccess) rc = NN4MG_EDEVICE;
     hier_use_stream(V, g->stream);
     if (rc) fail_member(S, g, mb, rc);
 }
 
-// Move a member on when its enqueued work has arrived.  ADMIT: the coarsest
-// inverse and its upload, then (ordered after the admission work and after
-// any batch in flight) the solve's start on the group stream.  FINISH: the
+// Move a member on when its enqueued work has arrived.  ADMIT: the check of
+// the coefficient, then (ordered after the admission work and after any batch
+// in flight) the solve's start on the group stream.  FINISH: the
 // result.
 bool advance_member(nn4mg_server *S, Group *g, Member &mb)
 {
@@ -475,12 +468,7 @@ bool advance_member(nn4mg_server *S, Group *g, Member &mb)
         return true;
     }
     int rc = NN4MG_OK;
-    if (mb.req.cfg.coef_mode == NN4MG_COEF_NODAL) {
-        hier_use_stream(V, g->admit);
-        rc = coef_end(V, mb.hk, mb.bad, mb.inv);
-        if (!rc && hipEventRecord(mb.ev, g->admit) != hipSuccess) rc = NN4MG_EDEVICE;
-        hier_use_stream(V, g->stream);
-    }
+    if (mb.req.cfg.coef_mode == NN4MG_COEF_NODAL) rc = coef_end(mb.bad);
     if (!rc && hipStreamWaitEvent(g->stream, mb.ev, 0) != hipSuccess) rc = NN4MG_EDEVICE;
     if (!rc) rc = solve_begin(V, hier_bw(V), hier_xw(V), mb.req.rtol, mb.req.max_cycles, 0);
     if (rc) {
