@@ -17,6 +17,7 @@
 #include <cstddef>
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -76,30 +77,49 @@ TileShape default_tiles(int nx, int ny, int nz, int zmul = 1)
     return make_tiles(nx, ny, nz, zc, best_tx);
 }
 
-// Longest z-chunk (power of two, at most 64) that keeps >= 512 workgroups
-// (two per compute unit) for a tile of tx x ty cells.
-int zchunk_for(int nx, int ny, int nz, int tx, int ty)
+// Launch shape of a z-marching pass: the tile width of `widths` and the z-chunk
+// for which the march is shortest.  A workgroup marches its chunk in zc + lead
+// steps (lead: planes staged before the first output), and the chip holds two
+// workgroups per compute unit (512) at once, so the workgroups run in rounds of
+// 512; a last round of at most 256, one per compute unit, takes `single` times
+// as long per step as a full one.  A shorter chunk fills the chip better and
+// repeats the lead more often; a chunk that leaves a few workgroups for another
+// round costs that whole round.  Measured per step: two-sweep pass 3.2 us in a
+// full round, 2.1 us in a single one (FP64; FP32 2.4 and 1.8), residual 1.35
+// and 0.95 us.  zmul: the launches cover that many copies of the level.
+TileShape march_tiles(int nx, int ny, int nz, int zmul, std::initializer_list<int> widths, int lead, double single)
 {
-    const long tiles = (long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
-    int zc = 64;
-    while (zc > 2 && tiles * ((nz + zc - 1) / zc) < 512) zc /= 2;
-    return zc;
+    TileShape best{};
+    double best_cost = 1e300, best_area = 1e300;
+    for (int tx : widths) {
+        const double area = (double)((nx + tx - 1) / tx * tx) * (double)((ny + 512 / tx - 1) / (512 / tx) * (512 / tx));
+        for (int zc = 2; zc <= 256 && zc <= nz + (nz & 1); zc += 2) {
+            const TileShape t = make_tiles(nx, ny, nz, zc, tx, 2);
+            const long long w = (long long)t.blocks() * zmul;
+            const long long rest = w % 512;
+            const double rounds = (double)(w / 512) + (rest == 0 ? 0.0 : rest <= 256 ? single : 1.0);
+            const double cost = rounds * (zc + lead);
+            if (cost < best_cost || (cost == best_cost && area < best_area)) {
+                best = t;
+                best_cost = cost;
+                best_area = area;
+            }
+        }
+    }
+    return best_cost < 1e300 ? best : make_tiles(nx, ny, nz, 2, 64, 2);
 }
 
-// Default shape per kernel class: the residual in 64-wide tiles of 2 rows per
-// thread; with the two-sweep pass (nu_post == 2) the first-sweep class in
-// 32-wide tiles, 2 rows per thread in FP64 and 1 with FP32 smoothing (the FP64
-// run state of 64-wide tiles leaves one wave per SIMD).  zmul: the launches
-// cover that many copies of the level (a batched group), so the z-chunk is
-// chosen for zmul times the workgroups.
-TileShape default_tiles_for(int nx, int ny, int nz, int kclass, bool mixed, bool fused, int zmul = 1)
+// Default shape per kernel class: the residual and (with nu_post == 2) the
+// two-sweep pass by march_tiles, in tiles of 512 cells (the FP64 run state of
+// the two-sweep pass in 64-wide tiles leaves one wave per SIMD).  A power-of-two
+// chunk that kept 512 workgroups, one row per thread with FP32 smoothing and
+// 64-wide residual tiles everywhere were slower: two-sweep pass and residual
+// at 96 x 64 x 160 (FP64) 38.7 and 18.5 us to 26.5 and 13.2 us, at 192 x 160 x
+// 224 (FP32) 90.7 and 43.7 us to 65 and 38 us.
+TileShape default_tiles_for(int nx, int ny, int nz, int kclass, bool fused, int zmul = 1)
 {
-    if (kclass == NN4MG_KCLASS_FINE_RESID && nx >= 64)
-        return make_tiles(nx, ny, nz, zchunk_for(nx, ny, nz * zmul, 64, 8), 64, 2);
-    if (kclass == NN4MG_KCLASS_FINE_SWEEP_PROLONG && fused && nx >= 32) {
-        const int ry = mixed ? 1 : 2;
-        return make_tiles(nx, ny, nz, zchunk_for(nx, ny, nz * zmul, 32, 8 * ry), 32, ry);
-    }
+    if (kclass == NN4MG_KCLASS_FINE_RESID) return march_tiles(nx, ny, nz, zmul, {64, 32, 16}, 2, 0.7);
+    if (kclass == NN4MG_KCLASS_FINE_SWEEP_PROLONG && fused) return march_tiles(nx, ny, nz, zmul, {32, 16}, 4, 0.66);
     return default_tiles(nx, ny, nz, zmul);
 }
 
@@ -926,7 +946,7 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         // depend on the group it runs in)
         const int zmul = group ? kGroupTileCopies : 1;
         for (int c = 0; c < 3; ++c)
-            V.tiles[c] = default_tiles_for(V.nx, V.ny, V.nz, c, H->mixed, cfg->nu_post == 2 && H->L >= 2, zmul);
+            V.tiles[c] = default_tiles_for(V.nx, V.ny, V.nz, c, cfg->nu_post == 2 && H->L >= 2, zmul);
         if (V.tiles[0].blocks() > maxblk) maxblk = V.tiles[0].blocks();
         if (nodal) TRY(dalloc(H, &V.k, V.n));
         const bool single = (H->L == 1);
@@ -1087,7 +1107,6 @@ int nn4mg_residual_noalloc(const nn4mg_config *cfg, const double *k_dev, const d
     const bool nodal = cfg->coef_mode == NN4MG_COEF_NODAL;
     if (nodal && !k_dev) return fail(NN4MG_EINVAL, "nodal coefficient mode needs k");
     const int L = count_levels(cfg->nx, cfg->ny, cfg->nz, cfg->min_coarse);
-    const bool mixed = cfg->precision != NN4MG_PREC_FP64;
     StencilArgs a;
     std::memset(&a, 0, sizeof(a));
     a.g.nx = cfg->nx;
@@ -1095,7 +1114,7 @@ int nn4mg_residual_noalloc(const nn4mg_config *cfg, const double *k_dev, const d
     a.g.nz = cfg->nz;
     for (int f = 0; f < 6; ++f) a.g.bc[f] = cfg->bc[f];
     // the launch shape nn4mg_setup gives the finest residual of this config
-    a.t = default_tiles_for(cfg->nx, cfg->ny, cfg->nz, NN4MG_KCLASS_FINE_RESID, mixed, cfg->nu_post == 2 && L >= 2);
+    a.t = default_tiles_for(cfg->nx, cfg->ny, cfg->nz, NN4MG_KCLASS_FINE_RESID, cfg->nu_post == 2 && L >= 2);
     a.h = cfg->h;
     a.omega = cfg->omega;
     a.yin = x_dev;
