@@ -179,7 +179,9 @@ struct nn4mg_hier {
     int L = 0;
     Level lv[kMaxLevels];
     int tail = 0;           // first level of the one-workgroup coarse end (0: none)
-    void *ktail = nullptr;  // padded coefficients of the tail levels (nodal; FP64, or FP32 when mixed)
+    void *ktail = nullptr;  // padded coefficients of the tail levels (nodal; FP64, or FP32 when mixed without dense)
+    double *dense = nullptr;  // the coarse end's matrix (see dense_kernel), or NULL: its one-workgroup kernel runs
+    bool use_dense = false;
     bool fused = false;     // both post-sweeps of a level in one pass (nu_post == 2)
     int singular = 0;
     int mixed = 0;
@@ -301,7 +303,61 @@ void release(nn4mg_hier *H)
     H->st_host = nullptr;
 }
 
-size_t bytes_for(const nn4mg_config *c)
+// The coarse end of the cycle runs in one workgroup from the first level whose
+// fields (right-hand side and two iterates per level, down to the coarsest)
+// fit the LDS budget.
+constexpr size_t kTailLdsBudget = 128 * 1024;
+// One compute unit sweeps a 16^3 level slower than the whole chip does including
+// its launch; up to about a thousand cells the single workgroup wins.
+constexpr size_t kTailMaxCells = 1024;
+
+// First level of the coarse end (0: none), and whether its one-workgroup kernel
+// fits in FP64, which the matrix of the dense form (dense_kernel) is built with.
+struct TailChoice {
+    int first = 0;
+    size_t cells = 0;  // of the first level
+    bool fits_f64 = false;
+};
+
+TailChoice choose_tail(const nn4mg_config *c)
+{
+    TailChoice out;
+    const int L = count_levels(c->nx, c->ny, c->nz, c->min_coarse);
+    if (L < 2) return out;
+    const size_t elt = c->precision != NN4MG_PREC_FP64 ? 4 : 8;
+    const int nodal = c->coef_mode == NN4MG_COEF_NODAL;
+    auto cells_of = [&](int l) { return (size_t)(c->nx >> l) * (c->ny >> l) * (c->nz >> l); };
+    auto padded_of = [&](int l) {
+        return (size_t)((c->nx >> l) + 2) * ((c->ny >> l) + 2) * ((c->nz >> l) + 2);
+    };
+    if (padded_of(L - 1) > 2 * kTailMaxCells) return out;  // no tail
+    auto field_cells = [&](int T) {
+        int nx[kTailMaxLevels], ny[kTailMaxLevels], nz[kTailMaxLevels];
+        for (int l = T; l < L; ++l) {
+            nx[l - T] = c->nx >> l;
+            ny[l - T] = c->ny >> l;
+            nz[l - T] = c->nz >> l;
+        }
+        return tail_field_cells(nx, ny, nz, L - T, nodal);
+    };
+    if (cells_of(L - 1) <= kTailMaxCells) out.first = L - 1;
+    for (int T = 1; T < L; ++T) {
+        if (L - T > kTailMaxLevels || cells_of(T) > kTailMaxCells) continue;
+        bool fits = true;  // the workgroup covers at most two padded cells per thread
+        for (int l = T; l < L; ++l) fits = fits && padded_of(l) <= 2 * kTailMaxCells;
+        if (fits && field_cells(T) * elt + 48 * 1024 <= kTailLdsBudget) {
+            out.first = T;
+            break;
+        }
+    }
+    if (out.first > 0) {
+        out.cells = cells_of(out.first);
+        out.fits_f64 = field_cells(out.first) * 8 + 48 * 1024 <= kTailLdsBudget;
+    }
+    return out;
+}
+
+size_t bytes_for(const nn4mg_config *c, bool dense)
 {
     const int L = count_levels(c->nx, c->ny, c->nz, c->min_coarse);
     const bool mixed = c->precision != NN4MG_PREC_FP64;
@@ -329,40 +385,10 @@ size_t bytes_for(const nn4mg_config *c)
     const size_t nc = (size_t)(c->nx >> (L - 1)) * (c->ny >> (L - 1)) * (c->nz >> (L - 1));
     b += 8 * nc * nc + sizeof(SolveState) + 8 * maxblk + 64 + 4 * kCoefFlags;
     b += kArenaAlign * (size_t)(5 * L + 12);  // alignment of each field in the arena
+    const TailChoice tail = choose_tail(c);
+    if (dense && tail.fits_f64) b += 8 * tail.cells * tail.cells;
     if (c->outer == NN4MG_OUTER_FCG) b += 4 * 8 * (size_t)c->nx * c->ny * c->nz + 8 * (size_t)fcg_partials_needed();
     return b;
-}
-
-// The coarse end of the cycle runs in one workgroup from the first level whose
-// fields (right-hand side and two iterates per level, down to the coarsest)
-// fit the LDS budget.
-constexpr size_t kTailLdsBudget = 128 * 1024;
-// One compute unit sweeps a 16^3 level slower than the whole chip does including
-// its launch; up to about a thousand cells the single workgroup wins.
-constexpr size_t kTailMaxCells = 1024;
-int choose_tail(const nn4mg_hier *H)
-{
-    if (H->L < 2) return 0;
-    const size_t elt = H->mixed ? 4 : 8;
-    const int nodal = H->cfg.coef_mode == NN4MG_COEF_NODAL;
-    const Level &C = H->lv[H->L - 1];
-    if ((size_t)(C.nx + 2) * (C.ny + 2) * (C.nz + 2) > 2 * kTailMaxCells) return 0;  // no tail
-    for (int T = 1; T < H->L; ++T) {
-        if (H->L - T > kTailMaxLevels) continue;
-        int nx[kTailMaxLevels], ny[kTailMaxLevels], nz[kTailMaxLevels];
-        bool fits = true;
-        for (int l = T; l < H->L; ++l) {
-            nx[l - T] = H->lv[l].nx;
-            ny[l - T] = H->lv[l].ny;
-            nz[l - T] = H->lv[l].nz;
-            // the workgroup covers at most two padded cells per thread
-            fits = fits && (size_t)(nx[l - T] + 2) * (ny[l - T] + 2) * (nz[l - T] + 2) <= 2 * kTailMaxCells;
-        }
-        if (!fits) continue;
-        const size_t cells = tail_field_cells(nx, ny, nz, H->L - T, nodal);
-        if (cells * elt + 48 * 1024 <= kTailLdsBudget && H->lv[T].n <= kTailMaxCells) return T;
-    }
-    return H->lv[H->L - 1].n <= kTailMaxCells ? H->L - 1 : 0;
 }
 
 // The coarse levels' coefficients from lv[0].k (nodal): coarsening, the
@@ -380,10 +406,11 @@ int enqueue_coef_kernels(nn4mg_hier *H)
             for (int l = 0; l < H->L; ++l) HIP_TRY(launch_cast_k(H->lv[l].k, H->lv[l].ks, H->lv[l].n, H->kts, s));
         if (H->ktail) {
             size_t off = 0;
-            const size_t elt = H->mixed ? sizeof(float) : sizeof(double);
+            const bool f64 = !H->mixed || H->use_dense;
+            const size_t elt = f64 ? sizeof(double) : sizeof(float);
             for (int l = H->tail; l < H->L; ++l) {
                 const Level &V = H->lv[l];
-                HIP_TRY(launch_tail_kpad(H->mixed ? 0 : 1, H->mixed ? H->kts : KT_F64,
+                HIP_TRY(launch_tail_kpad(f64 ? 1 : 0, H->mixed ? H->kts : KT_F64,
                                          H->mixed ? V.ks : (const void *)V.k, V.nx, V.ny, V.nz, c.bc,
                                          (char *)H->ktail + off * elt, s));
                 off += (size_t)(V.nx + 2) * (V.ny + 2) * (V.nz + 2);
@@ -393,8 +420,32 @@ int enqueue_coef_kernels(nn4mg_hier *H)
     return NN4MG_OK;
 }
 
+// The coarse end's levels, coefficients and parameters (no right-hand side yet).
+TailArgs tail_args(const nn4mg_hier *H)
+{
+    const int T = H->tail;
+    TailArgs ta;
+    std::memset(&ta, 0, sizeof(ta));
+    ta.levels = H->L - T;
+    for (int l = T; l < H->L; ++l) {
+        const Level &V = H->lv[l];
+        ta.nx[l - T] = V.nx;
+        ta.ny[l - T] = V.ny;
+        ta.nz[l - T] = V.nz;
+        ta.h[l - T] = V.h;
+    }
+    ta.kpad = H->ktail;
+    ta.ainv = H->ainv;
+    ta.ainv_in_lds = (size_t)H->nc * H->nc * 8 <= 48 * 1024;
+    ta.singular = H->singular;
+    for (int f = 0; f < 6; ++f) ta.bc[f] = H->cfg.bc[f];
+    ta.omega = H->cfg.omega;
+    ta.nu = H->cfg.nu_post;
+    return ta;
+}
+
 // Everything derived from the coefficient in lv[0].k, the coarsest inverse
-// included.
+// and the coarse end's matrix included.
 int enqueue_coefficients(nn4mg_hier *H)
 {
     const int rc = enqueue_coef_kernels(H);
@@ -413,6 +464,11 @@ int enqueue_coefficients(nn4mg_hier *H)
     a.ainv = H->ainv;
     a.flag = H->flag;
     HIP_TRY(launch_coarse_inverse(a, H->stream));
+    if (H->use_dense) {
+        TailArgs ta = tail_args(H);
+        ta.e_first = H->dense;
+        HIP_TRY(launch_tail_columns(H->cfg.coef_mode == NN4MG_COEF_NODAL ? KT_F64 : KT_NONE, ta, H->stream));
+    }
     return NN4MG_OK;
 }
 
@@ -712,8 +768,8 @@ int resid_blocks(const nn4mg_hier *H) { return H->lv[0].tiles[NN4MG_KCLASS_FINE_
 // Everything of one cycle after the finest residual has been restricted to
 // level 1 (FP64: lv[1].b; mixed: lv[1].b32 and the FP32 finest residual in
 // lv[0].b32).
-// stop_np > 0: the first restriction-chain launch also applies the stopping
-// rule to the stop_np norm partials in H->partials.
+// stop_np > 0 (stop_in_chain): the first launch also applies the stopping rule
+// to the stop_np norm partials in H->partials.
 // x_out: where the direct form of the finest sweeps puts the new iterate.
 int enqueue_cycle_body(nn4mg_hier *H, const double *b, const double *bmean, double *x, const int *done,
                        bool x_zero = false, int stop_np = 0, double *x_out = nullptr)
@@ -724,48 +780,58 @@ int enqueue_cycle_body(nn4mg_hier *H, const double *b, const double *bmean, doub
     int rc;
     if (H->tail > 0) {
         const int T = H->tail;
-        // right-hand sides of levels 2 .. T - 1, up to three levels per launch
-        for (int l = 1; l + 1 < T; l += 3) {
-            const int depth = std::min(3, T - 1 - l);
+        // right-hand sides of levels 2 .. T - 1, up to four levels per launch;
+        // the dense form takes level T's from them too, unless that would be
+        // a launch of its own
+        const int last = H->use_dense ? T : T - 1;
+        int l = 1;
+        bool stop = stop_np > 0;  // the stopping rule (on the residual the previous stationary cycle ended with,
+                                  // or on FCG's updated r) runs in the first of these launches
+        while (l < last && !(H->use_dense && l + 1 == T)) {
+            const int depth = std::min(4, last - l);
             Level &V = H->lv[l];
-            auto bof = [&](int m) -> void * {
-                if (m > l + depth) return nullptr;
-                return f64 ? (void *)H->lv[m].b : (void *)H->lv[m].b32;
-            };
-            // the first launch may also run the stopping rule (on the residual
-            // the previous stationary cycle ended with, or on FCG's updated r)
-            const bool stop_here = stop_np > 0 && l == 1;
-            HIP_TRY(launch_restrict_chain(f64 ? 1 : 0, f64 ? (void *)V.b : (void *)V.b32, bof(l + 1), bof(l + 2),
-                                          bof(l + 3), V.nx, V.ny, V.nz, depth, done, s, stop_here ? H->st : nullptr,
-                                          stop_here ? H->partials : nullptr, stop_here ? stop_np : 0, H->ncopy,
-                                          H->bstride));
+            void *c[4];
+            for (int m = 0; m < 4; ++m)
+                c[m] = m >= depth ? nullptr : f64 ? (void *)H->lv[l + 1 + m].b : (void *)H->lv[l + 1 + m].b32;
+            HIP_TRY(launch_restrict_chain(f64 ? 1 : 0, f64 ? (void *)V.b : (void *)V.b32, c, V.nx, V.ny, V.nz, depth,
+                                          done, s, stop ? H->st : nullptr, stop ? H->partials : nullptr,
+                                          stop ? stop_np : 0, H->ncopy, H->bstride));
+            stop = false;
+            l += depth;
         }
-        TailArgs ta;
-        std::memset(&ta, 0, sizeof(ta));
-        ta.levels = L - T;
-        for (int l = T; l < L; ++l) {
-            const Level &V = H->lv[l];
-            ta.nx[l - T] = V.nx;
-            ta.ny[l - T] = V.ny;
-            ta.nz[l - T] = V.nz;
-            ta.h[l - T] = V.h;
-        }
-        ta.kpad = H->ktail;
-        if (T >= 2)
-            ta.b_above = f64 ? (const void *)H->lv[T - 1].b : (const void *)H->lv[T - 1].b32;
+        const void *b_above = nullptr, *b_first = nullptr;
+        if (T >= 2 && !(H->use_dense && l == T))
+            b_above = f64 ? (const void *)H->lv[T - 1].b : (const void *)H->lv[T - 1].b32;
         else
-            ta.b_first = f64 ? (const void *)H->lv[T].b : (const void *)H->lv[T].b32;
-        ta.e_first = f64 ? (void *)H->lv[T].e : (void *)H->lv[T].e32;
-        ta.ainv = H->ainv;
-        ta.ainv_in_lds = (size_t)H->nc * H->nc * 8 <= 48 * 1024;
-        ta.singular = H->singular;
-        for (int f = 0; f < 6; ++f) ta.bc[f] = H->cfg.bc[f];
-        ta.omega = H->cfg.omega;
-        ta.nu = H->cfg.nu_post;
-        ta.done = done;
-        ta.ncopy = H->ncopy;
-        ta.bstride = H->bstride;
-        HIP_TRY(launch_tail(f64 ? 1 : 0, f64 ? H->kt64 : H->kts, ta, s));
+            b_first = f64 ? (const void *)H->lv[T].b : (const void *)H->lv[T].b32;
+        void *e = f64 ? (void *)H->lv[T].e : (void *)H->lv[T].e32;
+        if (H->use_dense) {
+            DenseArgs da;
+            std::memset(&da, 0, sizeof(da));
+            da.m = H->dense;
+            da.n = (int)H->lv[T].n;
+            da.nx = H->lv[T].nx;
+            da.ny = H->lv[T].ny;
+            da.b_above = b_above;
+            da.b = b_first;
+            da.e = e;
+            da.done = done;
+            da.st = stop ? H->st : nullptr;
+            da.partials = stop ? H->partials : nullptr;
+            da.np = stop ? stop_np : 0;
+            da.ncopy = H->ncopy;
+            da.bstride = H->bstride;
+            HIP_TRY(launch_dense(f64 ? 1 : 0, da, s));
+        } else {
+            TailArgs ta = tail_args(H);
+            ta.b_above = b_above;
+            ta.b_first = b_first;
+            ta.e_first = e;
+            ta.done = done;
+            ta.ncopy = H->ncopy;
+            ta.bstride = H->bstride;
+            HIP_TRY(launch_tail(f64 ? 1 : 0, f64 ? H->kt64 : H->kts, ta, s));
+        }
         for (int l = T - 1; l >= 1; --l)
             if ((rc = enqueue_coarse_sweeps(H, l, done))) return rc;
         return enqueue_fine_sweeps(H, b, bmean, x, done, x_zero, x_out);
@@ -815,10 +881,11 @@ int enqueue_single_level_body(nn4mg_hier *H, double *x, const int *done)
     return NN4MG_OK;
 }
 
-// The stationary solve's stopping rule runs inside the cycle's first
-// restriction-chain launch when there is one (levels between the finest and
-// the coarse end); otherwise as its own launch after each residual.
-bool stop_in_chain(const nn4mg_hier *H) { return H->L > 1 && H->tail > 2; }
+// The stationary solve's stopping rule runs inside the cycle's first launch
+// after the residual when that is a restriction chain (levels between the
+// finest and the coarse end) or the coarse end's product; otherwise as its own
+// launch after each residual.
+bool stop_in_chain(const nn4mg_hier *H) { return H->L > 1 && (H->tail > 2 || H->use_dense); }
 
 // One cycle body from x; the new iterate is in x, or (direct_fine) in x_out.
 int enqueue_body(nn4mg_hier *H, const double *b, const double *bmean, double *x, const int *done,
@@ -875,7 +942,7 @@ void nn4mg_config_default(nn4mg_config *cfg, int nx, int ny, int nz, double h)
 size_t nn4mg_bytes_required(const nn4mg_config *cfg)
 {
     if (validate(cfg) != NN4MG_OK) return 0;
-    return bytes_for(cfg);
+    return bytes_for(cfg, true);
 }
 
 const char *nn4mg_last_error(void) { return g_err.c_str(); }
@@ -896,7 +963,7 @@ int nn4mg_setup(const nn4mg_config *cfg, const double *k_dev, void *hip_stream, 
     int rc = validate(cfg);
     if (rc) return rc;
     if (cfg->coef_mode == NN4MG_COEF_NODAL && !k_dev) return fail(NN4MG_EINVAL, "nodal coefficient requires k");
-    return nn4mg::setup_hier(cfg, k_dev, (hipStream_t)hip_stream, 1, out);
+    return nn4mg::setup_hier(cfg, k_dev, (hipStream_t)hip_stream, 1, out, false, true);
 }
 
 }  // extern "C"
@@ -906,7 +973,7 @@ int nn4mg_setup(const nn4mg_config *cfg, const double *k_dev, void *hip_stream, 
 // right-hand side and iterate fields, and each copy's coefficient is set up
 // through its view.
 int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t stream, int ncopy, nn4mg_hier **out,
-                      bool group)
+                      bool group, bool dense)
 {
     *out = nullptr;
     if (ncopy < 1 || (ncopy > 1 && !group)) return fail(NN4MG_EINVAL, "several copies are a batched group");
@@ -971,7 +1038,9 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         }
     const Level &C = H->lv[H->L - 1];
     H->nc = (int)C.n;
-    H->tail = choose_tail(H);
+    const TailChoice tail = choose_tail(cfg);
+    H->tail = tail.first;
+    H->use_dense = dense && tail.fits_f64;
     H->fused = cfg->nu_post == 2 && H->L >= 2;
     if (group && (H->L < 2 || H->tail == 0 || !H->fused || cfg->outer != NN4MG_OUTER_STATIONARY)) {
         nn4mg_destroy(H);
@@ -985,9 +1054,10 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         size_t cells = 0;
         for (int l = H->tail; l < H->L; ++l)
             cells += (size_t)(H->lv[l].nx + 2) * (H->lv[l].ny + 2) * (H->lv[l].nz + 2);
-        TRY(dalloc_bytes(H, &H->ktail, cells * (H->mixed ? sizeof(float) : sizeof(double))));
+        TRY(dalloc_bytes(H, &H->ktail, cells * (H->mixed && !H->use_dense ? sizeof(float) : sizeof(double))));
     }
     TRY(dalloc(H, &H->ainv, (size_t)H->nc * H->nc));
+    if (H->use_dense) TRY(dalloc(H, &H->dense, tail.cells * tail.cells));
     TRY(dalloc(H, &H->st, 1));
     TRY(dalloc(H, &H->partials, (size_t)maxblk));
     H->max_partials = maxblk;
@@ -1391,6 +1461,8 @@ bool capture_iteration(nn4mg_hier *H, const double *b, double *x, int par)
 }  // namespace
 
 namespace nn4mg {
+
+size_t hier_bytes(const nn4mg_config *cfg, bool dense) { return validate(cfg) == NN4MG_OK ? bytes_for(cfg, dense) : 0; }
 
 // ---- asynchronous solve pieces (used by nn4mg_solve and the server) ----
 

@@ -139,13 +139,33 @@ struct SolveState {
 hipError_t launch_stencil(int T_is_f64, int kt, int in_mode, int out_mode, int out_f32, const StencilArgs &a,
                           hipStream_t s);
 
-// depth (1..3) successive restrictions from the level of dims nx x ny x nz into c1, c2, c3 (one launch).
+// depth (1..4) successive restrictions from the level of dims nx x ny x nz into c1 .. c4 (one launch).
 // With st, one extra workgroup applies the stopping rule to the np residual
 // partials (skipped when a stand-alone launch marked them taken).
-hipError_t launch_restrict_chain(int T_is_f64, const void *fine, void *c1, void *c2, void *c3, int nx, int ny, int nz,
-                                 int depth, const int *done, hipStream_t s, SolveState *st = nullptr,
+hipError_t launch_restrict_chain(int T_is_f64, const void *fine, void *const c[4], int nx, int ny, int nz, int depth,
+                                 const int *done, hipStream_t s, SolveState *st = nullptr,
                                  const double *partials = nullptr, int np = 0, int ncopy = 1,
                                  long long bstride = 0);
+
+// The coarse end of the cycle as one matrix: e = M b on a level of n <= 1024
+// cells (m[j * n + i] = M_ij, FP64; b and e of type T).  b_above: the
+// right-hand side of the level above (dims 2 nx x 2 ny x 2 nz), restricted
+// here; else b is the level's own.  With st, one extra workgroup applies the
+// stopping rule as in launch_restrict_chain.
+struct DenseArgs {
+    const double *m;
+    int n, nx, ny;
+    const void *b_above, *b;
+    void *e;
+    const int *done;
+    SolveState *st;
+    const double *partials;
+    int np;
+    int ncopy;
+    int nbc;  // workgroups per copy (set by the launcher)
+    long long bstride;
+};
+hipError_t launch_dense(int T_is_f64, const DenseArgs &a, hipStream_t s);
 hipError_t launch_restrict(int T_is_f64, const void *fine, void *coarse, int nx, int ny, int nz, const int *done,
                            hipStream_t s);
 hipError_t launch_coarsen_k(const double *kf, double *kc, int nx, int ny, int nz, int harmonic, hipStream_t s);
@@ -204,8 +224,11 @@ int solve_header_copy(nn4mg_hier *H);
 // every copy whose stopping rule has not fired, then the batch-end rule
 // (hier_mark_idle: set a copy's stopping flag, for copies with no solve).
 // hier_note_enqueued: record on a view that n cycles were enqueued for it.
+// dense: the coarse end as one matrix where there is one (8 n^2 bytes per copy
+// more, n <= 1024 cells); hier_bytes: device bytes of one copy (0: invalid).
 int setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t stream, int ncopy, nn4mg_hier **out,
-               bool group = false);
+               bool group, bool dense);
+size_t hier_bytes(const nn4mg_config *cfg, bool dense);
 int view_create(nn4mg_hier *G, int c, nn4mg_hier **out);
 void view_destroy(nn4mg_hier *V);
 double *hier_bw(nn4mg_hier *H);
@@ -287,6 +310,8 @@ struct TailArgs {
                                         // first, built by launch_tail_kpad; NULL if constant
     const void *b_above;                // right-hand side of the level above the first tail level, or NULL
     const void *b_first;                // right-hand side of the first tail level (when b_above is NULL)
+    int columns;                        // 1: workgroup c takes the c-th unit right-hand side (b_above and b_first
+                                        // NULL) and writes its correction to row c of e_first
     void *e_first;                      // out: correction of the first tail level
     const double *ainv;                 // coarsest inverse (FP64, symmetric)
     int ainv_in_lds;                    // stage the inverse in LDS (it fits)
@@ -302,6 +327,9 @@ struct TailArgs {
 // (nodal) the coefficient per level, the last three with a one-cell halo.
 size_t tail_field_cells(const int *nx, const int *ny, const int *nz, int levels, int nodal);
 size_t tail_lds_bytes(const TailArgs &a, int t_is_f64, int nodal);
+// The coarse end as a matrix: a's correction for every unit right-hand side,
+// row by row into e_first (FP64, n x n for n cells of the first tail level).
+hipError_t launch_tail_columns(int kt, TailArgs a, hipStream_t s);
 // Padded copy (one-cell halo by the +mirror rule) of a level's coefficient k
 // (storage type kt) as type T (double if T_is_f64, else float), for the tail.
 hipError_t launch_tail_kpad(int T_is_f64, int kt, const void *k, int nx, int ny, int nz, const int *bc, void *out,

@@ -68,14 +68,33 @@ __device__ double reduce_512(const double *p, int n, double *red)
     return s;
 }
 
-// Up to three successive restrictions (sum of the 8 children) in one launch:
-// each workgroup owns a 16^3 block of the input level and writes the 8^3, 4^3
-// and 2^3 blocks of the next levels under it.  A coarse cell depends only on
-// its own children, so no workgroup waits for another.  Sums in the order of
-// restrict_kernel (x pairs, then y, then z), so the results are the same.
+// The stopping rule on np residual partials by a whole 512-thread workgroup,
+// unless a stand-alone launch already took this residual.
+__device__ void stop_workgroup(SolveState *st, const double *partials, int np)
+{
+    __shared__ double red[8];
+    __shared__ int taken;
+    // one thread reads and clears the flag; every thread branches on the
+    // shared copy, so no wave can read it after the clear
+    if (threadIdx.x == 0) {
+        taken = st->taken;
+        st->taken = 0;
+    }
+    __syncthreads();
+    if (taken) return;  // uniform
+    const double s = reduce_512(partials, np, red);
+    if (threadIdx.x == 0) stop_rule(st, s);
+}
+
+// Up to four successive restrictions (sum of the 8 children) in one launch:
+// each workgroup owns a 16^3 block of the input level and writes the 8^3, 4^3,
+// 2^3 blocks and the one cell of the next levels under it.  A coarse cell
+// depends only on its own children, so no workgroup waits for another.  Sums in
+// the order of restrict_kernel (x pairs, then y, then z), so the results are
+// the same.
 template <typename T>
-__global__ __launch_bounds__(512) void restrict_chain_kernel(const T *f, T *c1, T *c2, T *c3, int nx, int ny, int nz,
-                                                             int depth, const int *done, SolveState *st,
+__global__ __launch_bounds__(512) void restrict_chain_kernel(const T *f, T *c1, T *c2, T *c3, T *c4, int nx, int ny,
+                                                             int nz, int depth, const int *done, SolveState *st,
                                                              const double *partials, int np, int nbc,
                                                              long long bstride)
 {
@@ -90,6 +109,7 @@ __global__ __launch_bounds__(512) void restrict_chain_kernel(const T *f, T *c1, 
         c1 = copy_ptr(c1, off);
         c2 = copy_ptr(c2, off);
         c3 = copy_ptr(c3, off);
+        c4 = copy_ptr(c4, off);
         done = copy_ptr(done, off);
         st = copy_ptr(st, off);
         partials = copy_ptr(partials, off);
@@ -97,24 +117,13 @@ __global__ __launch_bounds__(512) void restrict_chain_kernel(const T *f, T *c1, 
     if (done && *done) return;
     if (st && g == 0) {
         // the extra first workgroup (dispatched first, so its reduction is off
-        // the chain's critical path): stopping rule of the residual the
-        // previous cycle ended with, unless a stand-alone launch already took it
-        __shared__ double red[8];
-        __shared__ int taken;
-        // one thread reads and clears the flag; every thread branches on the
-        // shared copy, so no wave can read it after the clear
-        if (threadIdx.x == 0) {
-            taken = st->taken;
-            st->taken = 0;
-        }
-        __syncthreads();
-        if (taken) return;  // uniform
-        const double s = reduce_512(partials, np, red);
-        if (threadIdx.x == 0) stop_rule(st, s);
+        // the chain's critical path)
+        stop_workgroup(st, partials, np);
         return;
     }
     __shared__ T s1[512];  // the 8^3 block of the first coarse level
     __shared__ T s2[64];   // the 4^3 block of the second
+    __shared__ T s3[8];    // the 2^3 block of the third
     const int bxn = (nx + 15) / 16, byn = (ny + 15) / 16;
     const int bid = st ? g - 1 : g;
     const int bx = bid % bxn, rest = bid / bxn;
@@ -153,13 +162,105 @@ __global__ __launch_bounds__(512) void restrict_chain_kernel(const T *f, T *c1, 
     if (t < 8) {
         const int ni = t & 1, nj = (t >> 1) & 1, nk = t >> 2;
         const int I = bx * 2 + ni, J = by * 2 + nj, K = bz * 2 + nk;
+        T v = (T)0;
         if (I < ex && J < ey && K < ez) {
             const int o = 2 * ni + 8 * nj + 32 * nk;
-            c3[(size_t)I + (size_t)ex * ((size_t)J + (size_t)ey * (size_t)K)] =
-                ((s2[o] + s2[o + 1]) + (s2[o + 4] + s2[o + 5])) + ((s2[o + 16] + s2[o + 17]) + (s2[o + 20] + s2[o + 21]));
+            v = ((s2[o] + s2[o + 1]) + (s2[o + 4] + s2[o + 5])) + ((s2[o + 16] + s2[o + 17]) + (s2[o + 20] + s2[o + 21]));
+            c3[(size_t)I + (size_t)ex * ((size_t)J + (size_t)ey * (size_t)K)] = v;
         }
+        s3[t] = v;
+    }
+    if (depth < 4) return;
+    __syncthreads();
+    if (t == 0 && bx < (ex >> 1) && by < (ey >> 1) && bz < (ez >> 1))
+        c4[(size_t)bx + (size_t)(ex >> 1) * ((size_t)by + (size_t)(ey >> 1) * (size_t)bz)] =
+            ((s3[0] + s3[1]) + (s3[2] + s3[3])) + ((s3[4] + s3[5]) + (s3[6] + s3[7]));
+}
+
+// The coarse end of the cycle as a dense product, e = M b.  From the first
+// level of at most 1024 cells down, restriction, coarsest solve, prolongation
+// and sweeps are linear in that level's right-hand side, so they are one n x n
+// matrix, built with the coefficient (by the one-workgroup kernel on the n unit
+// vectors, launch_tail_columns).  The one-workgroup kernel is a chain of phases
+// on one compute unit (9 to 27 us a cycle); the product is spread over the chip
+// and bound by one round of loads: n = 512 reads 2 MB.  A workgroup takes 16
+// rows: 16 lanes along the row index (128 contiguous bytes of each matrix
+// column), 32 groups along the columns, summed in a fixed order.
+// With the one-workgroup kernel and with the product: 12 cycles at 64^3 641 and
+// 584 us, update and 20 cycles at 96 x 64 x 160 2.28 and 1.93 ms, a time step at
+// 32 x 32 x 64 (whose stopping rule moved in here too) 1.69 and 1.25 ms.
+constexpr int kDenseRows = 16, kDenseGroups = 512 / kDenseRows, kDenseAhead = 16;
+
+template <typename T>
+__global__ __launch_bounds__(512) void dense_kernel(const DenseArgs a)
+{
+    __shared__ double sb[1024];
+    __shared__ double part[512 / 64][kDenseRows];
+    int g = (int)blockIdx.x;
+    long long off = 0;
+    if (a.ncopy > 1) {
+        const int c = g / a.nbc;
+        g -= c * a.nbc;
+        off = (long long)c * a.bstride;
+    }
+    const int *done = copy_ptr(a.done, off);
+    // the stopping flag is read with the first loads and tested before any write
+    const int stop = done ? *done : 0;
+    if (a.st) {
+        if (g == 0) {
+            if (!stop) stop_workgroup(copy_ptr(a.st, off), copy_ptr(a.partials, off), a.np);
+            return;
+        }
+        g -= 1;
+    }
+    const double *m = copy_ptr(a.m, off);
+    const int n = a.n, t = threadIdx.x;
+    const int il = t & (kDenseRows - 1), jg = t / kDenseRows, i = g * kDenseRows + il;
+    const int ic = min(i, n - 1);
+    double v[kDenseAhead];  // the first 512 columns, in flight with the right-hand side
+#pragma unroll
+    for (int q = 0; q < kDenseAhead; ++q) {
+        const int j = jg + q * kDenseGroups;
+        v[q] = m[(size_t)min(j, n - 1) * n + ic];
+    }
+    if (a.b_above) {
+        const T *f = copy_ptr((const T *)a.b_above, off);
+        const size_t sy = 2 * (size_t)a.nx, sz = sy * 2 * (size_t)a.ny;
+        for (int c = t; c < n; c += 512) {
+            const int I = c % a.nx, r = c / a.nx;
+            const int J = r % a.ny, K = r / a.ny;
+            const size_t o = 2 * (size_t)I + sy * 2 * (size_t)J + sz * 2 * (size_t)K;
+            sb[c] = (double)(((f[o] + f[o + 1]) + (f[o + sy] + f[o + sy + 1])) +
+                             ((f[o + sz] + f[o + sz + 1]) + (f[o + sz + sy] + f[o + sz + sy + 1])));
+        }
+    } else {
+        const T *b = copy_ptr((const T *)a.b, off);
+        for (int c = t; c < n; c += 512) sb[c] = (double)b[c];
+    }
+    if (stop) return;  // uniform over the workgroup
+    __syncthreads();
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < kDenseAhead; q += 2) {
+        const int j = jg + q * kDenseGroups;
+        if (j < n) s0 = fma(v[q], sb[j], s0);
+        if (j + kDenseGroups < n) s1 = fma(v[q + 1], sb[j + kDenseGroups], s1);
+    }
+#pragma unroll 8
+    for (int j = jg + kDenseAhead * kDenseGroups; j < n; j += kDenseGroups) s0 = fma(m[(size_t)j * n + ic], sb[j], s0);
+    s0 += s1;
+    s0 += __shfl_xor(s0, 16);
+    s0 += __shfl_xor(s0, 32);
+    if ((t & 63) < kDenseRows) part[t >> 6][il] = s0;
+    __syncthreads();
+    if (t < kDenseRows && i < n) {
+        double e = 0.0;
+#pragma unroll
+        for (int w = 0; w < 512 / 64; ++w) e += part[w][il];
+        copy_ptr((T *)a.e, off)[i] = (T)e;
     }
 }
+
 
 __global__ __launch_bounds__(256) void coarsen_k_kernel(const double *f, double *c, int nx, int ny, int nz,
                                                         int harmonic)
@@ -379,11 +480,11 @@ hipError_t launch_restrict(int T_is_f64, const void *fine, void *coarse, int nx,
     return hipGetLastError();
 }
 
-hipError_t launch_restrict_chain(int T_is_f64, const void *fine, void *c1, void *c2, void *c3, int nx, int ny, int nz,
-                                 int depth, const int *done, hipStream_t s, SolveState *st, const double *partials,
-                                 int np, int ncopy, long long bstride)
+hipError_t launch_restrict_chain(int T_is_f64, const void *fine, void *const c[4], int nx, int ny, int nz, int depth,
+                                 const int *done, hipStream_t s, SolveState *st, const double *partials, int np,
+                                 int ncopy, long long bstride)
 {
-    if (depth < 1 || depth > 3) return hipErrorInvalidValue;
+    if (depth < 1 || depth > 4) return hipErrorInvalidValue;
     if (st && (!partials || np < 1)) return hipErrorInvalidValue;
     const unsigned nb = (unsigned)(((nx + 15) / 16) * ((ny + 15) / 16) * ((nz + 15) / 16));
     const unsigned per = st ? nb + 1 : nb;
@@ -391,11 +492,27 @@ hipError_t launch_restrict_chain(int T_is_f64, const void *fine, void *c1, void 
     const dim3 grid(batched ? per * (unsigned)ncopy : per);
     const int nbc = batched ? (int)per : 0;
     if (T_is_f64)
-        hipLaunchKernelGGL(restrict_chain_kernel<double>, grid, dim3(512), 0, s, (const double *)fine, (double *)c1,
-                           (double *)c2, (double *)c3, nx, ny, nz, depth, done, st, partials, np, nbc, bstride);
+        hipLaunchKernelGGL(restrict_chain_kernel<double>, grid, dim3(512), 0, s, (const double *)fine, (double *)c[0],
+                           (double *)c[1], (double *)c[2], (double *)c[3], nx, ny, nz, depth, done, st, partials, np,
+                           nbc, bstride);
     else
-        hipLaunchKernelGGL(restrict_chain_kernel<float>, grid, dim3(512), 0, s, (const float *)fine, (float *)c1,
-                           (float *)c2, (float *)c3, nx, ny, nz, depth, done, st, partials, np, nbc, bstride);
+        hipLaunchKernelGGL(restrict_chain_kernel<float>, grid, dim3(512), 0, s, (const float *)fine, (float *)c[0],
+                           (float *)c[1], (float *)c[2], (float *)c[3], nx, ny, nz, depth, done, st, partials, np,
+                           nbc, bstride);
+    return hipGetLastError();
+}
+
+hipError_t launch_dense(int T_is_f64, const DenseArgs &a_, hipStream_t s)
+{
+    DenseArgs a = a_;
+    if (a.n < 1 || a.n > 1024 || !a.m || !a.e || (!a.b_above && !a.b)) return hipErrorInvalidValue;
+    if (a.st && (!a.partials || a.np < 1)) return hipErrorInvalidValue;
+    a.nbc = (a.n + kDenseRows - 1) / kDenseRows + (a.st ? 1 : 0);
+    const dim3 grid((unsigned)a.nbc * (unsigned)(a.ncopy > 1 ? a.ncopy : 1));
+    if (T_is_f64)
+        hipLaunchKernelGGL(dense_kernel<double>, grid, dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL(dense_kernel<float>, grid, dim3(512), 0, s, a);
     return hipGetLastError();
 }
 

@@ -134,10 +134,20 @@ struct nn4mg_server {
 
 namespace {
 
-size_t request_bytes(const nn4mg_config &cfg)
+size_t request_bytes(const nn4mg_config &cfg, bool dense)
 {
     const size_t n = (size_t)cfg.nx * cfg.ny * cfg.nz;
-    return nn4mg_bytes_required(&cfg) + 2 * n * sizeof(double);
+    return hier_bytes(&cfg, dense) + 2 * n * sizeof(double);
+}
+
+// Whether requests of cfg run with the coarse end as a matrix (8 n^2 bytes per
+// copy, up to 8 MiB): only where the budget holds a full group that way, so a
+// small budget admits what it admits without.  Fixed for a server and a
+// configuration, so results do not depend on the load.
+bool dense_requests(const nn4mg_server *S, const nn4mg_config &cfg)
+{
+    const int cap = S->max_active < kGroupCap ? S->max_active : kGroupCap;
+    return (size_t)cap * request_bytes(cfg, true) <= S->budget;
 }
 
 void push_result(nn4mg_server *S, const Request &q, double t_start, const nn4mg_info &info, int status,
@@ -232,10 +242,11 @@ int acquire_resident(nn4mg_server *S, Slot &sl, int *err)
             return (int)i;
         }
     }
-    if (!make_room(S, request_bytes(q.cfg))) return -1;
+    const bool dense = dense_requests(S, q.cfg);
+    if (!make_room(S, request_bytes(q.cfg, dense))) return -1;
     Resident R;
     R.cfg = q.cfg;
-    if ((*err = nn4mg_setup(&q.cfg, q.k, (void *)sl.stream, &R.H))) return -2;
+    if ((*err = setup_hier(&q.cfg, q.k, sl.stream, 1, &R.H, false, dense))) return -2;
     if (hipMalloc((void **)&R.bw, q.n * sizeof(double)) != hipSuccess ||
         hipMalloc((void **)&R.xw, q.n * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
@@ -315,11 +326,6 @@ bool batchable(const nn4mg_server *S, const nn4mg_config &cfg)
     return true;
 }
 
-size_t group_bytes(const nn4mg_config &cfg, int cap)
-{
-    return (size_t)cap * request_bytes(cfg);
-}
-
 void destroy_group_objects(Group *g)
 {
     if (g->stream) (void)hipStreamSynchronize(g->stream);
@@ -377,9 +383,10 @@ Group *create_group(nn4mg_server *S, const nn4mg_config &cfg)
     // as many copies as fit the budget, up to the running-request limit and
     // kGroupCap; fewer (halving) while busy work holds the memory
     int cap = S->max_active < kGroupCap ? S->max_active : kGroupCap;
-    const size_t per = request_bytes(cfg);
+    const bool dense = dense_requests(S, cfg);
+    const size_t per = request_bytes(cfg, dense);
     if ((size_t)cap * per > S->budget) cap = (int)(S->budget / per);
-    while (cap >= 1 && !make_room(S, group_bytes(cfg, cap))) cap /= 2;
+    while (cap >= 1 && !make_room(S, (size_t)cap * per)) cap /= 2;
     if (cap < 1) return nullptr;
     Group *g = new Group();
     g->cfg = cfg;
@@ -390,7 +397,7 @@ Group *create_group(nn4mg_server *S, const nn4mg_config &cfg)
         destroy_group_objects(g);
         return nullptr;
     }
-    const int rc = setup_hier(&cfg, nullptr, g->stream, cap, &g->G, true);
+    const int rc = setup_hier(&cfg, nullptr, g->stream, cap, &g->G, true, dense);
     if (rc) {
         (void)hipGetLastError();
         g->G = nullptr;
@@ -666,7 +673,7 @@ int nn4mg_server_submit(nn4mg_srv_t S, const nn4mg_config *cfg, const double *k,
     if (cfg->coef_mode == NN4MG_COEF_NODAL && !k) return set_error(NN4MG_EINVAL, "server submit: NULL k for NODAL");
     const size_t need = nn4mg_bytes_required(cfg);
     if (need == 0) return set_error(NN4MG_EINVAL, "server submit: invalid configuration");
-    if (request_bytes(*cfg) > S->budget) return set_error(NN4MG_EBUSY, "server submit: request exceeds the whole budget");
+    if (request_bytes(*cfg, false) > S->budget) return set_error(NN4MG_EBUSY, "server submit: request exceeds the whole budget");
     Request q;
     q.tag = tag;
     q.cfg = *cfg;

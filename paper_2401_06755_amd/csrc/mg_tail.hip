@@ -18,6 +18,12 @@
 // +mirror).  Input: the right-hand side of the first tail level, or of the
 // level above it (then restricted here); output: the correction of the first
 // tail level, in HBM, for the prolongation into the next finer level.
+//
+// All of this is linear in the right-hand side, so it is also one matrix of at
+// most 1024 x 1024: with room for it (a stand-alone hierarchy, and the groups of
+// a server whose budget holds them) the kernel runs only when the coefficient is
+// set, one workgroup per unit right-hand side (launch_tail_columns, in FP64),
+// and the cycle applies the matrix (dense_kernel).
 #include "mg_internal.h"
 
 #include <type_traits>
@@ -246,6 +252,7 @@ __global__ __launch_bounds__(TT) void tail_kernel(const TailArgs a)
     const T *b_first_p = copy_ptr((const T *)a.b_first, coff);
     const double *ainv_p = copy_ptr(a.ainv, coff);
     T *e_first_p = copy_ptr((T *)a.e_first, coff);
+    if (a.columns) e_first_p += (size_t)blockIdx.x * (size_t)(a.nx[0] * a.ny[0] * a.nz[0]);
     constexpr bool HK = !std::is_same<KT, NoK>::value;
     extern __shared__ __align__(16) unsigned char smem[];
     T *sm = (T *)smem;
@@ -307,7 +314,7 @@ __global__ __launch_bounds__(TT) void tail_kernel(const TailArgs a)
             const T v4 = in[g + sz], v5 = in[g + sz + 1], v6 = in[g + sz + sy], v7 = in[g + sz + sy + 1];
             rb = ((v0 + v1) + (v2 + v3)) + ((v4 + v5) + (v6 + v7));
         } else {
-            rb = b_first_p[c];
+            rb = a.columns ? (T)(c == (int)blockIdx.x) : b_first_p[c];
         }
     }
     // padded coefficients (contiguous) and the coarsest inverse, first parts in registers
@@ -494,9 +501,14 @@ hipError_t launch_tail_kpad(int T_is_f64, int kt, const void *k, int nx, int ny,
     for (int f = 0; f < 6; ++f) b.v[f] = bc[f];
     const int pn = (nx + 2) * (ny + 2) * (nz + 2);
     const dim3 grid((pn + 255) / 256), block(256);
-    if (T_is_f64) {
-        if (kt != KT_F64) return hipErrorInvalidValue;
+    if (T_is_f64 && kt == KT_F64) {
         hipLaunchKernelGGL((kpad_kernel<double, double>), grid, block, 0, s, (const double *)k, nx, ny, nz, b,
+                           (double *)out);
+    } else if (T_is_f64 && kt == KT_F32) {
+        hipLaunchKernelGGL((kpad_kernel<double, float>), grid, block, 0, s, (const float *)k, nx, ny, nz, b,
+                           (double *)out);
+    } else if (T_is_f64 && kt == KT_F16) {
+        hipLaunchKernelGGL((kpad_kernel<double, __half>), grid, block, 0, s, (const __half *)k, nx, ny, nz, b,
                            (double *)out);
     } else if (kt == KT_F32) {
         hipLaunchKernelGGL((kpad_kernel<float, float>), grid, block, 0, s, (const float *)k, nx, ny, nz, b,
@@ -517,11 +529,13 @@ hipError_t launch_tail(int T_is_f64, int kt, const TailArgs &a, hipStream_t s)
     for (int l = 0; l < a.levels; ++l)
         if ((a.nx[l] + 2) * (a.ny[l] + 2) * (a.nz[l] + 2) > 2 * TT) return hipErrorInvalidValue;
     if (kt != KT_NONE && !a.kpad) return hipErrorInvalidValue;
+    if (a.columns ? (a.ncopy > 1 || a.b_above || !T_is_f64) : (!a.b_above && !a.b_first)) return hipErrorInvalidValue;
     const size_t lds = tail_lds_bytes(a, T_is_f64, kt != KT_NONE);
+    const unsigned grid = a.columns ? a.nx[0] * a.ny[0] * a.nz[0] : a.ncopy > 1 ? a.ncopy : 1;
     auto go = [&](auto kernel) -> hipError_t {
         hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(a.ncopy > 1 ? a.ncopy : 1), dim3(TT), lds, s, a);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(TT), lds, s, a);
         return hipGetLastError();
     };
     if (T_is_f64) {
@@ -533,6 +547,16 @@ hipError_t launch_tail(int T_is_f64, int kt, const TailArgs &a, hipStream_t s)
     if (kt == KT_F32) return go(tail_kernel<float, float>);
     if (kt == KT_F16) return go(tail_kernel<float, __half>);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_tail_columns(int kt, TailArgs a, hipStream_t s)
+{
+    a.b_above = nullptr;
+    a.b_first = nullptr;
+    a.done = nullptr;
+    a.ncopy = 1;
+    a.columns = 1;
+    return launch_tail(1, kt, a, s);
 }
 
 }  // namespace nn4mg
