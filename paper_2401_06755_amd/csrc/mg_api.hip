@@ -219,14 +219,7 @@ struct nn4mg_hier {
     const nn4mg_hier *view_of = nullptr;
     double *bw = nullptr, *xw = nullptr;  // batched: per-copy right-hand side and iterate
     std::vector<void *> allocs;
-    // captured hipGraphs of one stationary iteration (body + residual + stopping
-    // rule), from x into lv[0].t and back (one graph unless the finest sweeps
-    // take the direct form)
-    hipGraphExec_t graph[2] = {nullptr, nullptr};
-    const double *graph_b = nullptr;
-    double *graph_x = nullptr;
-    bool graphs_ok = true;  // cleared after a capture failure
-    int tiles_epoch = 0, graph_epoch = -1;
+    bool graphs_ok = true;  // group: cleared after a capture failure
     // async solve bookkeeping
     double solve_rtol = 0.0;
     int solve_max = 0, solve_fixed = 0, solve_enqueued = 0, solve_planned = 0;
@@ -287,10 +280,6 @@ void release(nn4mg_hier *H)
 {
     if (H->view_of) return;  // a view owns nothing
     if (H->stream) (void)hipStreamSynchronize(H->stream);
-    for (hipGraphExec_t &g : H->graph) {
-        if (g) (void)hipGraphExecDestroy(g);
-        g = nullptr;
-    }
     for (hipGraphExec_t &g : H->bgraph) {
         if (g) (void)hipGraphExecDestroy(g);
         g = nullptr;
@@ -1354,7 +1343,7 @@ int enqueue_iteration(nn4mg_hier *H, const double *b, double *x, int par)
     return enqueue_stationary_iteration(H, b, x, par);
 }
 
-// Parity of iteration `index` of a solve: which graph (and buffer order) it uses.
+// Parity of iteration `index` of a solve: which buffer order it uses.
 int iteration_parity(const nn4mg_hier *H, int index)
 {
     return (H->cfg.outer != NN4MG_OUTER_FCG && direct_fine(H)) ? (index & 1) : 0;
@@ -1413,51 +1402,6 @@ int finish_solve(nn4mg_hier *H, double *x, nn4mg_info *info, std::chrono::steady
     return finish_complete(H, info, t0);
 }
 
-// Capture one stationary iteration of parity `par` on the handle's stream as
-// a graph bound to (b, x).  Returns false (and launches nothing) if capture is
-// not possible.
-bool capture_iteration(nn4mg_hier *H, const double *b, double *x, int par)
-{
-    if (!H->graphs_ok || H->stream == nullptr || H->prof_on) return false;
-    if (H->graph_b != b || H->graph_x != x || H->graph_epoch != H->tiles_epoch) {
-        for (hipGraphExec_t &ge : H->graph)
-            if (ge) {
-                (void)hipGraphExecDestroy(ge);
-                ge = nullptr;
-            }
-        H->graph_b = b;
-        H->graph_x = x;
-        H->graph_epoch = H->tiles_epoch;
-    }
-    if (H->graph[par]) return true;
-    hipGraph_t g = nullptr;
-    if (hipStreamBeginCapture(H->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-        (void)hipGetLastError();
-        H->graphs_ok = false;
-        return false;
-    }
-    const int saved_tag = H->cur_tag;
-    const int rc = enqueue_iteration(H, b, x, par);
-    H->cur_tag = saved_tag;
-    const hipError_t e = hipStreamEndCapture(H->stream, &g);
-    if (rc != NN4MG_OK || e != hipSuccess || !g) {
-        (void)hipGetLastError();
-        if (g) (void)hipGraphDestroy(g);
-        H->graphs_ok = false;
-        return false;
-    }
-    hipGraphExec_t ex = nullptr;
-    const hipError_t ie = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (ie != hipSuccess) {
-        (void)hipGetLastError();
-        H->graphs_ok = false;
-        return false;
-    }
-    H->graph[par] = ex;
-    return true;
-}
-
 }  // namespace
 
 namespace nn4mg {
@@ -1487,21 +1431,18 @@ int solve_begin(nn4mg_hier *H, const double *b, double *x, double rtol, int max_
     return NN4MG_OK;
 }
 
-// Enqueue the next planned batch of cycles (as graph launches when possible).
+// Enqueue the next planned batch of cycles, launch by launch: back to back on
+// the stream they leave no gaps, while a graph of one cycle, captured anew for
+// every pair of buffers, cost 3 to 6 us per replay on top of its kernels (16
+// cycles: 64^3 Poisson 688 us against 646, 128^3 with FP32 smoothing 1288
+// against 1196, 96 x 64 x 160 1211 against 1110).
 int solve_enqueue_next(nn4mg_hier *H, const double *b, double *x)
 {
     int rc;
     const int n = H->solve_planned;
     if (n <= 0) return NN4MG_OK;
-    const int p0 = iteration_parity(H, H->solve_enqueued), p1 = iteration_parity(H, H->solve_enqueued + 1);
-    if (capture_iteration(H, b, x, p0) && (n == 1 || capture_iteration(H, b, x, p1))) {
-        for (int c = 0; c < n; ++c)
-            HIP_TRY(hipGraphLaunch(H->graph[iteration_parity(H, H->solve_enqueued + c)], H->stream));
-        H->cur_tag += n;
-    } else {
-        for (int c = 0; c < n; ++c)
-            if ((rc = enqueue_iteration(H, b, x, iteration_parity(H, H->solve_enqueued + c)))) return rc;
-    }
+    for (int c = 0; c < n; ++c)
+        if ((rc = enqueue_iteration(H, b, x, iteration_parity(H, H->solve_enqueued + c)))) return rc;
     // the last residual of the batch is judged before the host reads the state
     if (H->cfg.outer != NN4MG_OUTER_FCG && stop_in_chain(H))
         HIP_TRY(launch_finish_norm(H->st, H->partials, resid_blocks(H), H->stream, 1));
@@ -1591,11 +1532,8 @@ int view_create(nn4mg_hier *G, int c, nn4mg_hier **out)
     V->arena = nullptr;
     V->allocs.clear();
     V->fields.clear();
-    V->graph[0] = V->graph[1] = nullptr;
     V->bgraph.clear();
     V->cap = 1;
-    V->graph_b = nullptr;
-    V->graph_x = nullptr;
     V->prof_on = false;
     V->prof_ev.clear();
     V->prof_cls.clear();
@@ -1793,7 +1731,6 @@ int nn4mg_set_tiles(nn4mg_t H, int level, int kclass, int tx, int ry, int zc)
             return fail(NN4MG_EINVAL, "the 8^3 block shape needs nu_post == 2 and a level of at least 4^3");
         HIP_TRY(hipStreamSynchronize(H->stream));
         H->lv[level].block2 = true;
-        H->tiles_epoch++;
         return NN4MG_OK;
     }
     if ((tx != 64 && tx != 32 && tx != 16) || (ry != 1 && ry != 2 && ry != 4) || (tx == 16 && ry == 4) || zc < 2 ||
@@ -1811,7 +1748,6 @@ int nn4mg_set_tiles(nn4mg_t H, int level, int kclass, int tx, int ry, int zc)
         if (kclass < 0 || kclass == c) V.tiles[c] = t;
     }
     if (kclass < 0 || kclass == NN4MG_KCLASS_FINE_SWEEP_PROLONG) V.block2 = false;
-    H->tiles_epoch++;
     return NN4MG_OK;
 }
 
@@ -1930,7 +1866,6 @@ int nn4mg_autotune(nn4mg_t H, const double *b, double *x, int *tiles_out, int ma
             }
         }
     }
-    H->tiles_epoch++;
     H->prof_on = saved_on;
     clear();
     if (tiles_out)

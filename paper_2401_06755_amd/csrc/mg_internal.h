@@ -198,7 +198,7 @@ hipError_t launch_add(double *x, const void *e, int e_f32, size_t n, const int *
 
 // ---- asynchronous solve pieces over a hierarchy (mg_api.hip) ----
 // begin: reset the device state, b-norm, first residual; enqueue_next: the next
-// planned batch of cycles (graph launches when the stream allows capture);
+// planned batch of cycles;
 // header_async: copy the state header to pinned host memory and record ev;
 // after_header (once ev completed): 1 when finished, else plans the next batch;
 // finish: projection / zero fill, full state read-back (synchronous).
