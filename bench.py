@@ -61,9 +61,10 @@ BYTES_PER_CELL = {
               "sweeps": 1 + 8 + 8 + 8,
               "sweep": 8 + 8 + 8},
 }
-# FP64 with the finest sweeps in the 8^3 block form (an autotuner choice on
-# small grids): the correction is smoothed against the full residual r, which
-# the residual kernel writes out, and added into x.
+# FP64 with the finest sweeps as 8^3 blocks in the correction form (a batched
+# group's; a stand-alone hierarchy's blocks take the direct form): the
+# correction is smoothed against the full residual r, which the residual kernel
+# writes out, and added into x.
 BYTES_PER_CELL_BLOCK = {
     "fp64": {"resid": 8 + 8 + 8 + 8 + 1,      # x, b, k; r, restricted residual
              "sweeps": 1 + 8 + 8 + 8 + 8,     # e_1, r, k; x read + write
@@ -77,6 +78,8 @@ BYTES_PER_CELL_BLOCK = {
 def fine_bytes(mode, res):
     """Bytes per finest cell of each kernel class in the run `res`."""
     tiles = res.get("tiles")
+    if res.get("direct"):
+        return BYTES_PER_CELL[mode]
     if mode in BYTES_PER_CELL_BLOCK and tiles and list(tiles[0][1]) == [8, 8, 8]:
         return BYTES_PER_CELL_BLOCK[mode]
     return BYTES_PER_CELL[mode]
@@ -207,7 +210,7 @@ def run_solver(nn4mg, torch, work, precision, steps, warmup, rtol, autotune=True
     H.close()
     return dict(n=n, dt=dt, dt_prof=dt_prof, cycles=cycles, info=infos[-1], kern=kern, levels=levels,
                 x=xd if keep_x else None,
-                setup_ms=setup_ms,
+                direct=True, setup_ms=setup_ms,
                 update_ms=update_ms, tiles=tiles, tune_ms=tune_ms,
                 all_converged=all(i.status == 0 for i in infos))
 

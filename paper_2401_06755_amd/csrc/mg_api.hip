@@ -588,8 +588,8 @@ TileShape sweep2_tiles(const nn4mg_hier *H, int l)
 }
 
 // Both sweeps of level l from P e_{l+1} against the right-hand side b:
-// out_mode OUT_STORE into y, or OUT_ADD64 into x64.  With xin (FP64, marching
-// form only): from xin + P e_{l+1} against b - bmean, stored into y != xin.
+// out_mode OUT_STORE into y, or OUT_ADD64 into x64.  With xin (FP64): from
+// xin + P e_{l+1} against b - bmean, stored into y != xin.
 int enqueue_sweep2(nn4mg_hier *H, int l, const void *b, void *y, double *x64, int out_mode, const int *done,
                    const double *xin = nullptr, const double *bmean = nullptr)
 {
@@ -605,17 +605,22 @@ int enqueue_sweep2(nn4mg_hier *H, int l, const void *b, void *y, double *x64, in
     a.x64 = x64;
     a.done = done;
     const long pr = prof_begin(H, NN4MG_KCLASS_FINE_SWEEP_PROLONG, l);
-    if (xin)
-        HIP_TRY(launch_sweep2(1, H->kt64, IN_PROLONG_ADD, OUT_STORE, a, H->stream));
-    else if (H->lv[l].block2)
-        HIP_TRY(launch_sweep2_block(f64 ? 1 : 0, f64 ? H->kt64 : H->kts, out_mode, a, H->stream));
+    const int in_mode = xin ? IN_PROLONG_ADD : IN_PROLONG;
+    if (H->lv[l].block2)
+        HIP_TRY(launch_sweep2_block(f64 ? 1 : 0, f64 ? H->kt64 : H->kts, in_mode, out_mode, a, H->stream));
     else
-        HIP_TRY(launch_sweep2(f64 ? 1 : 0, f64 ? H->kt64 : H->kts, IN_PROLONG, out_mode, a, H->stream));
+        HIP_TRY(launch_sweep2(f64 ? 1 : 0, f64 ? H->kt64 : H->kts, in_mode, out_mode, a, H->stream));
     prof_end(H, pr);
     return NN4MG_OK;
 }
 
-// Largest coarse level that defaults to the 8^3 block form of the two sweeps.
+// Largest level that defaults to the block form of the two sweeps: its time
+// grows with the cells from the start, that of a march over z with its chain of
+// plane steps.  Blocks and best march, us: 32^3 FP64 nodal 8.8 and 14.5, 48^3
+// 13.8 and 16.6, 64^3 17.0 and 16.1 (constant 14.3 and 14.8, FP32 9.5 and 12.1),
+// 64 x 64 x 128 27.4 and 20.2.  Over several copies the cells count together (as in
+// kGroupTileCopies): 8 copies of a 64^3 level in FP32 took 47 us in blocks, while
+// a march over as many cells takes 27.
 constexpr size_t kBlock2MaxCells = 64 * 64 * 64;
 
 bool level_fusable(const nn4mg_hier *H, int l)
@@ -624,17 +629,17 @@ bool level_fusable(const nn4mg_hier *H, int l)
     return H->fused && V.nx >= 4 && V.ny >= 4 && V.nz >= 4;
 }
 
-// FP64 cycles whose finest sweeps run in the marching two-sweep pass take the
-// direct form x' = S S (x + P e_1) against b - bmean: the finest residual
-// kernel then writes only R r and the norm partials (no full r), and the pass
-// reads x on its two-cell ring, so x' goes to a second buffer (lv[0].t) and
-// successive cycles alternate between x and lv[0].t.
+// FP64 cycles with both finest sweeps in one pass take the direct form
+// x' = S S (x + P e_1) against b - bmean: the finest residual kernel then
+// writes only R r and the norm partials (no full r), and the pass reads x on
+// its two-cell ring, so x' goes to a second buffer (lv[0].t) and successive
+// cycles alternate between x and lv[0].t.
 bool direct_fine(const nn4mg_hier *H)
 {
     // batched hierarchies and their views keep the correction form: the copies
     // of a batch run from different cycle counts, so no common buffer order
     if (H->group || H->view_of) return false;
-    return !H->mixed && H->L > 1 && level_fusable(H, 0) && !H->lv[0].block2;
+    return !H->mixed && H->L > 1 && level_fusable(H, 0);
 }
 
 // nu_post Jacobi sweeps at level l >= 1 (first input: P e_{l+1}); result in e.
@@ -688,8 +693,8 @@ int enqueue_fine_sweeps(nn4mg_hier *H, const double *b, const double *bmean, dou
             if (!x_out || x_out == x) return fail(NN4MG_EINVAL, "direct finest sweeps need a second buffer");
             return enqueue_sweep2(H, 0, b, x_out, nullptr, OUT_STORE, done, x, bmean);
         }
-        // the 8^3 block form: the correction is smoothed against the full
-        // residual the residual kernel wrote into F.t
+        // a batched group: the correction is smoothed against the full residual
+        // the residual kernel wrote into F.t
         return enqueue_sweep2(H, 0, F.t, nullptr, x, OUT_ADD64, done);
     }
     if (!H->mixed) {
@@ -850,8 +855,8 @@ int enqueue_resid_for_cycle(nn4mg_hier *H, const double *b, const double *x, con
     }
     if (H->mixed)
         return enqueue_resid(H, x, b, bmean, H->lv[0].b32, H->lv[1].b32, true, with_norm, done);
-    // the 8^3 block form of the finest sweeps smooths the correction against
-    // the full residual; the direct form needs none
+    // a batched group smooths the correction against the full residual; the
+    // direct form needs none
     const bool full = H->fused && !direct_fine(H);
     return enqueue_resid(H, x, b, bmean, full ? H->lv[0].t : nullptr, H->lv[1].b, false, with_norm, done);
 }
@@ -1036,9 +1041,9 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         return fail(NN4MG_EINVAL, "no batched form: needs the stationary cycle, two post-sweeps and a one-workgroup "
                                   "coarse end");
     }
-    // coarse levels of up to 64^3 cells: the block form of the two sweeps is
-    // shorter than a march over z (the autotuner re-decides per level)
-    for (int l = 1; l < H->L; ++l) H->lv[l].block2 = level_fusable(H, l) && H->lv[l].n <= kBlock2MaxCells;
+    // (the autotuner re-decides per level)
+    for (int l = 0; l < H->L; ++l)
+        H->lv[l].block2 = level_fusable(H, l) && H->lv[l].n * (group ? kGroupTileCopies : 1) <= kBlock2MaxCells;
     if (nodal && H->tail > 0) {
         size_t cells = 0;
         for (int l = H->tail; l < H->L; ++l)

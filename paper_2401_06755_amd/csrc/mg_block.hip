@@ -28,28 +28,34 @@ namespace nn4mg {
 
 namespace {
 
-// Corner and cross sums of the 3x3 neighbourhood of o in a plane with row stride W.
+// What the plane of o (row stride W) adds to the sum S of the cell at o in the
+// same plane (2 D) and in a neighbouring one (2 X + D).
 template <typename T, int W>
-__device__ __forceinline__ T dsum(const T *v, int o)
+__device__ __forceinline__ T own_plane(const T *v, int o)
 {
-    return (v[o - W - 1] + v[o - W + 1]) + (v[o + W - 1] + v[o + W + 1]);
+    const T D = corner_sum(v[o - W - 1] + v[o - W + 1], v[o + W - 1] + v[o + W + 1]);
+    return D + D;
 }
 template <typename T, int W>
-__device__ __forceinline__ T xsum(const T *v, int o)
+__device__ __forceinline__ T other_plane(const T *v, int o)
 {
-    return (v[o - W] + v[o + W]) + (v[o - 1] + v[o + 1]);
+    const T D = corner_sum(v[o - W - 1] + v[o - W + 1], v[o + W - 1] + v[o + W + 1]);
+    return neighbour_plane(D, cross_sum(v[o - W], v[o + W], v[o - 1] + v[o + 1]));
 }
 // The same for the product k v, k with its own strides.
 template <typename T, int W, int WK>
-__device__ __forceinline__ T dprod(const T *v, int o, const T *k, int ok)
+__device__ __forceinline__ T corner_prod(const T *v, int o, const T *k, int ok)
 {
-    return (k[ok - WK - 1] * v[o - W - 1] + k[ok - WK + 1] * v[o - W + 1]) +
-           (k[ok + WK - 1] * v[o + W - 1] + k[ok + WK + 1] * v[o + W + 1]);
+    return corner_sum(pair_prod(k[ok - WK - 1], v[o - W - 1], k[ok - WK + 1], v[o - W + 1]),
+                      pair_prod(k[ok + WK - 1], v[o + W - 1], k[ok + WK + 1], v[o + W + 1]));
 }
 template <typename T, int W, int WK>
-__device__ __forceinline__ T xprod(const T *v, int o, const T *k, int ok)
+__device__ __forceinline__ T other_prod(const T *v, int o, const T *k, int ok)
 {
-    return (k[ok - WK] * v[o - W] + k[ok + WK] * v[o + W]) + (k[ok - 1] * v[o - 1] + k[ok + 1] * v[o + 1]);
+#pragma clang fp contract(off)
+    const T ma = k[ok - WK] * v[o - W], mc = k[ok + WK] * v[o + W];
+    return neighbour_plane(corner_prod<T, W, WK>(v, o, k, ok),
+                           cross_sum(ma, mc, pair_prod(k[ok - 1], v[o - 1], k[ok + 1], v[o + 1])));
 }
 
 // One Jacobi update of the cell at c of field v (row stride W, plane stride WP);
@@ -58,24 +64,15 @@ __device__ __forceinline__ T xprod(const T *v, int o, const T *k, int ok)
 template <typename T, bool HK, int W, int WP, int WK, int WKP>
 __device__ __forceinline__ T jacobi_at(const T *v, int c, const T *k, int ck, T bb, T cw, T om_w0, T om, T icv)
 {
-    const T y0 = v[c];
-    const T Dz = dsum<T, W>(v, c);
-    const T Sx = (Dz + Dz + fma((T)2, xsum<T, W>(v, c - WP), dsum<T, W>(v, c - WP))) +
-                 fma((T)2, xsum<T, W>(v, c + WP), dsum<T, W>(v, c + WP));
+    const T Sx = (own_plane<T, W>(v, c) + other_plane<T, W>(v, c - WP)) + other_plane<T, W>(v, c + WP);
     if constexpr (!HK) {
-        return y0 + om_w0 * (bb - cw * (Sx - (T)32 * y0));
+        return jacobi_const(v[c], Sx, bb, cw, om_w0);
     } else {
-        const T kc = k[ck];
-        const T Dk = dsum<T, WK>(k, ck);
-        const T Sk = (Dk + Dk + fma((T)2, xsum<T, WK>(k, ck - WKP), dsum<T, WK>(k, ck - WKP))) +
-                     fma((T)2, xsum<T, WK>(k, ck + WKP), dsum<T, WK>(k, ck + WKP));
-        const T Dp = dprod<T, W, WK>(v, c, k, ck);
-        const T Sp = (Dp + Dp + fma((T)2, xprod<T, W, WK>(v, c - WP, k, ck - WKP),
-                                    dprod<T, W, WK>(v, c - WP, k, ck - WKP))) +
-                     fma((T)2, xprod<T, W, WK>(v, c + WP, k, ck + WKP), dprod<T, W, WK>(v, c + WP, k, ck + WKP));
-        const T Dg = fma((T)32, kc, Sk);
-        const T Ays = Dg * y0 - kc * Sx - Sp;
-        return y0 + om * (bb * icv - Ays) * recip(Dg);
+        const T Sk = (own_plane<T, WK>(k, ck) + other_plane<T, WK>(k, ck - WKP)) + other_plane<T, WK>(k, ck + WKP);
+        const T Dp = corner_prod<T, W, WK>(v, c, k, ck);
+        const T Sp = ((Dp + Dp) + other_prod<T, W, WK>(v, c - WP, k, ck - WKP)) +
+                     other_prod<T, W, WK>(v, c + WP, k, ck + WKP);
+        return jacobi_nodal(v[c], k[ck], Sx, Sk, Sp, bb, om, icv);
     }
 }
 
@@ -94,9 +91,13 @@ struct BlockShape {
     static_assert(CN <= NT && ON <= NT, "one coarse cell and at most one output cell per thread");
 };
 
-template <typename T, typename KT, int OUT, int E>
+// XIN: the first sweep's input is x + P e (x = a.yin on the staged region), the
+// right-hand side b - bmean, the output stored into a.yout, which must not alias
+// a.yin (neighbouring blocks read it on their rings).
+template <typename T, typename KT, int OUT, bool XIN, int E>
 __global__ __launch_bounds__(BlockShape<E>::NT) void sweep2_block_kernel(const StencilArgs a_)
 {
+    static_assert(!(XIN && OUT == OUT_ADD64), "the x + P e input form stores its result");
     using S = BlockShape<E>;
     constexpr int NT = S::NT, PE = S::PE, PN = S::PN, QE = S::QE, QN = S::QN, CE = S::CE, CN = S::CN;
     constexpr int NP = S::NP, NQ = S::NQ;
@@ -139,7 +140,9 @@ __global__ __launch_bounds__(BlockShape<E>::NT) void sweep2_block_kernel(const S
         cval = s < 0 ? -v : v;
     }
     typename KStore<T, KT>::type kr[HK ? NP : 1];
-    if constexpr (HK) {
+    T xr[XIN ? NP : 1];
+    const T bm = (XIN && a.bmean) ? (T)*a.bmean : (T)0;
+    if constexpr (HK || XIN) {
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
             const int idx = min(q * NT + t, PN - 1);
@@ -148,7 +151,12 @@ __global__ __launch_bounds__(BlockShape<E>::NT) void sweep2_block_kernel(const S
             const int fi = fold(i0 + px - 2, nx, a.g.bc[0], a.g.bc[1], s);
             const int fj = fold(j0 + py - 2, ny, a.g.bc[2], a.g.bc[3], s);
             const int fk = fold(k0 + pz - 2, nz, a.g.bc[4], a.g.bc[5], s);
-            kr[q] = kp[(size_t)fi + (size_t)nx * ((size_t)fj + (size_t)ny * (size_t)fk)];
+            const size_t f = (size_t)fi + (size_t)nx * ((size_t)fj + (size_t)ny * (size_t)fk);
+            if constexpr (HK) kr[q] = kp[f];
+            if constexpr (XIN) {
+                const T v = ((const T *)a.yin)[f];
+                xr[q] = s < 0 ? -v : v;
+            }
         }
     }
     T bq[NQ];  // first-sweep right-hand side, signed by the halo rule
@@ -160,7 +168,7 @@ __global__ __launch_bounds__(BlockShape<E>::NT) void sweep2_block_kernel(const S
         const int fi = fold(i0 + qx - 1, nx, a.g.bc[0], a.g.bc[1], s);
         const int fj = fold(j0 + qy - 1, ny, a.g.bc[2], a.g.bc[3], s);
         const int fk = fold(k0 + qz - 1, nz, a.g.bc[4], a.g.bc[5], s);
-        const T v = bp[(size_t)fi + (size_t)nx * ((size_t)fj + (size_t)ny * (size_t)fk)];
+        const T v = bp[(size_t)fi + (size_t)nx * ((size_t)fj + (size_t)ny * (size_t)fk)] - bm;
         bq[q] = s < 0 ? -v : v;
     }
     // this thread's output cell (threads beyond the block's cells only stage)
@@ -169,7 +177,7 @@ __global__ __launch_bounds__(BlockShape<E>::NT) void sweep2_block_kernel(const S
     const int gi = i0 + ox, gj = j0 + oy, gk = k0 + oz;
     const bool valid = t < S::ON && gi < nx && gj < ny && gk < nz;
     const size_t g = (size_t)min(gi, nx - 1) + (size_t)nx * ((size_t)min(gj, ny - 1) + (size_t)ny * (size_t)min(gk, nz - 1));
-    const T b2 = bp[g];
+    const T b2 = bp[g] - bm;
     double xo = 0.0;
     if constexpr (ADD) xo = a.x64[g];
     if (stop) return;  // uniform over the workgroup
@@ -192,13 +200,16 @@ __global__ __launch_bounds__(BlockShape<E>::NT) void sweep2_block_kernel(const S
             const int I = (ui >> 1) - ((i0 >> 1) - 2), J = (uj >> 1) - ((j0 >> 1) - 2);
             const int K = (uk >> 1) - ((k0 >> 1) - 2);
             const int dI = (ui & 1) ? 1 : -1, dJ = (uj & 1) ? CE : -CE, dK = (uk & 1) ? CE * CE : -CE * CE;
-            const T w3 = (T)0.75, wq = (T)0.25;
             const int c00 = I + CE * J + CE * CE * K;
-            const T z00 = w3 * sc[c00] + wq * sc[c00 + dK];
-            const T z01 = w3 * sc[c00 + dI] + wq * sc[c00 + dI + dK];
-            const T z10 = w3 * sc[c00 + dJ] + wq * sc[c00 + dJ + dK];
-            const T z11 = w3 * sc[c00 + dJ + dI] + wq * sc[c00 + dJ + dI + dK];
-            sx[idx] = w3 * (w3 * z00 + wq * z01) + wq * (w3 * z10 + wq * z11);
+            const T z00 = lerp31(sc[c00], sc[c00 + dK]);
+            const T z01 = lerp31(sc[c00 + dI], sc[c00 + dI + dK]);
+            const T z10 = lerp31(sc[c00 + dJ], sc[c00 + dJ + dK]);
+            const T z11 = lerp31(sc[c00 + dJ + dI], sc[c00 + dJ + dI + dK]);
+            const T pe = lerp31(lerp31(z00, z01), lerp31(z10, z11));
+            if constexpr (XIN)
+                sx[idx] = xr[q] + pe;
+            else
+                sx[idx] = pe;
         }
     }
     __syncthreads();
@@ -232,7 +243,7 @@ __global__ __launch_bounds__(BlockShape<E>::NT) void sweep2_block_kernel(const S
 // most compute units idle runs faster as more, smaller blocks.
 constexpr int kSmallBlockBelow = 256;
 
-template <typename T, typename KT, int OUT>
+template <typename T, typename KT, int OUT, bool XIN = false>
 hipError_t goB(const StencilArgs &a_, hipStream_t s)
 {
     StencilArgs a = a_;
@@ -240,10 +251,10 @@ hipError_t goB(const StencilArgs &a_, hipStream_t s)
     if ((long long)nb8 * (a.ncopy > 1 ? a.ncopy : 1) < kSmallBlockBelow) {
         const int nb4 = ((a.g.nx + 3) / 4) * ((a.g.ny + 3) / 4) * ((a.g.nz + 3) / 4);
         const unsigned grid = batched_grid(a, nb4);
-        hipLaunchKernelGGL((sweep2_block_kernel<T, KT, OUT, 4>), dim3(grid), dim3(BlockShape<4>::NT), 0, s, a);
+        hipLaunchKernelGGL((sweep2_block_kernel<T, KT, OUT, XIN, 4>), dim3(grid), dim3(BlockShape<4>::NT), 0, s, a);
     } else {
         const unsigned grid = batched_grid(a, nb8);
-        hipLaunchKernelGGL((sweep2_block_kernel<T, KT, OUT, 8>), dim3(grid), dim3(BlockShape<8>::NT), 0, s, a);
+        hipLaunchKernelGGL((sweep2_block_kernel<T, KT, OUT, XIN, 8>), dim3(grid), dim3(BlockShape<8>::NT), 0, s, a);
     }
     return hipGetLastError();
 }
@@ -255,10 +266,17 @@ int block2_blocks(int nx, int ny, int nz)
     return ((nx + 7) / 8) * ((ny + 7) / 8) * ((nz + 7) / 8);
 }
 
-hipError_t launch_sweep2_block(int T_is_f64, int kt, int out_mode, const StencilArgs &a, hipStream_t s)
+hipError_t launch_sweep2_block(int T_is_f64, int kt, int in_mode, int out_mode, const StencilArgs &a, hipStream_t s)
 {
     if (a.g.nx < 2 || a.g.ny < 2 || a.g.nz < 2) return hipErrorInvalidValue;
-    if (a.bmean || !a.ec || !a.b) return hipErrorInvalidValue;
+    if (!a.ec || !a.b) return hipErrorInvalidValue;
+    if (in_mode == IN_PROLONG_ADD) {  // as launch_sweep2: FP64, stored into another buffer
+        if (!T_is_f64 || out_mode != OUT_STORE || !a.yin || !a.yout || a.yin == a.yout) return hipErrorInvalidValue;
+        if (kt == KT_NONE) return goB<double, NoK, OUT_STORE, true>(a, s);
+        if (kt == KT_F64) return goB<double, double, OUT_STORE, true>(a, s);
+        return hipErrorInvalidValue;
+    }
+    if (in_mode != IN_PROLONG || a.bmean) return hipErrorInvalidValue;
     if (T_is_f64) {
         if (out_mode == OUT_STORE) {
             if (kt == KT_NONE) return goB<double, NoK, OUT_STORE>(a, s);

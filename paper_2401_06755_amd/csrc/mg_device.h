@@ -54,6 +54,65 @@ __device__ __forceinline__ float recip(float d)
     return fmaf(fmaf(-d, r, 1.0f), r, r);
 }
 
+// ---- one Jacobi update, operation by operation.  Both forms of the two-sweep
+// pass (the z-march and the blocks) go through these functions, with every
+// fused multiply-add written out and none left to the compiler, so a cell's
+// result is the same bit for bit whichever form a level takes.
+
+// k y summed over a pair of cells.
+template <typename T>
+__device__ __forceinline__ T pair_prod(T k0, T v0, T k1, T v1)
+{
+#pragma clang fp contract(off)
+    const T p = k0 * v0;
+    return fma(k1, v1, p);
+}
+
+// Corner and cross sums of a plane from its three rows: side pairs h, centres m.
+template <typename T>
+__device__ __forceinline__ T corner_sum(T ha, T hc)
+{
+    return ha + hc;
+}
+template <typename T>
+__device__ __forceinline__ T cross_sum(T ma, T mc, T hb)
+{
+#pragma clang fp contract(off)
+    return (ma + mc) + hb;
+}
+// What a plane adds to the cell of a neighbouring plane: 2 X + D.
+template <typename T>
+__device__ __forceinline__ T neighbour_plane(T D, T X)
+{
+    return fma((T)2, X, D);
+}
+
+// y + omega (b - A y) / D with the sums S of y, k and k y; cw = -h/12,
+// om_w0 = omega / (8h/3), icv = 24/h.
+template <typename T>
+__device__ __forceinline__ T jacobi_const(T y0, T Sx, T bb, T cw, T om_w0)
+{
+    return fma(om_w0, fma(-cw, fma((T)-32, y0, Sx), bb), y0);
+}
+template <typename T>
+__device__ __forceinline__ T jacobi_nodal(T y0, T k0, T Sx, T Sk, T Sp, T bb, T om, T icv)
+{
+#pragma clang fp contract(off)
+    const T Dg = fma((T)32, k0, Sk);
+    const T Ays = fma(Dg, y0, -fma(k0, Sx, Sp));
+    const T w = om * fma(bb, icv, -Ays);
+    return fma(w, recip(Dg), y0);
+}
+
+// Cell-centred linear interpolation along one axis: 3/4 near + 1/4 far.
+template <typename T>
+__device__ __forceinline__ T lerp31(T near, T far)
+{
+#pragma clang fp contract(off)
+    const T f = (T)0.25 * far;
+    return fma((T)0.75, near, f);
+}
+
 // Halo index -> interior index, flipping the sign across a Dirichlet-zero
 // wall.  Indices beyond the one-cell halo (ragged tiles) are clamped into
 // range; their values are never used by a valid output.

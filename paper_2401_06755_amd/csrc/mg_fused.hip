@@ -154,6 +154,7 @@ struct Row {
 template <typename T, bool HK>
 __device__ __forceinline__ Row<T> row_at(const T *v, int c, const T *k, int ck)
 {
+#pragma clang fp contract(off)
     Row<T> o;
     const T vl = v[c - 1], vm = v[c], vr = v[c + 1];
     o.h = vl + vr;
@@ -162,7 +163,7 @@ __device__ __forceinline__ Row<T> row_at(const T *v, int c, const T *k, int ck)
         const T kl = k[ck - 1], km = k[ck], kr = k[ck + 1];
         o.kh = kl + kr;
         o.km = km;
-        o.ph = kl * vl + kr * vr;
+        o.ph = pair_prod(kl, vl, kr, vr);
         o.pm = km * vm;
     }
     return o;
@@ -173,21 +174,17 @@ template <typename T, bool HK>
 __device__ __forceinline__ PS<T> col_sums(const Row<T> &a, const Row<T> &b, const Row<T> &c)
 {
     PS<T> o;
-    const T D = a.h + c.h;
-    const T X = (a.m + c.m) + b.h;
+    const T D = corner_sum(a.h, c.h);
     o.xc = b.m;
     o.xa = D + D;
-    o.xo = fma((T)2, X, D);
+    o.xo = neighbour_plane(D, cross_sum(a.m, c.m, b.h));
     if constexpr (HK) {
-        const T Dk = a.kh + c.kh;
-        const T Xk = (a.km + c.km) + b.kh;
-        const T Dp = a.ph + c.ph;
-        const T Xp = (a.pm + c.pm) + b.ph;
+        const T Dk = corner_sum(a.kh, c.kh), Dp = corner_sum(a.ph, c.ph);
         o.kc = b.km;
         o.ka = Dk + Dk;
-        o.ko = fma((T)2, Xk, Dk);
+        o.ko = neighbour_plane(Dk, cross_sum(a.km, c.km, b.kh));
         o.pa = Dp + Dp;
-        o.po = fma((T)2, Xp, Dp);
+        o.po = neighbour_plane(Dp, cross_sum(a.pm, c.pm, b.ph));
     }
     return o;
 }
@@ -211,16 +208,10 @@ __device__ __forceinline__ void absorb(Run<T> &r, const PS<T> &p, bool first)
 template <typename T, bool HK>
 __device__ __forceinline__ T jacobi(const Run<T> &r, const PS<T> &p, T bb, T cw, T om_w0, T om, T icv)
 {
-    const T y0 = r.xc;
-    if constexpr (!HK) {
-        const T S = r.qx + p.xo;
-        return y0 + om_w0 * (bb - cw * (S - (T)32 * y0));
-    } else {
-        const T Sx = r.qx + p.xo, Sk = r.qk + p.ko, Sp = r.qp + p.po;
-        const T Dg = fma((T)32, r.kc, Sk);
-        const T Ays = Dg * y0 - r.kc * Sx - Sp;
-        return y0 + om * (bb * icv - Ays) * recip(Dg);
-    }
+    if constexpr (!HK)
+        return jacobi_const(r.xc, r.qx + p.xo, bb, cw, om_w0);
+    else
+        return jacobi_nodal(r.xc, r.kc, r.qx + p.xo, r.qk + p.ko, r.qp + p.po, bb, om, icv);
 }
 
 // XIN: the first sweep's input is x + P e (x = a.yin, the right-hand side
@@ -344,11 +335,10 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
         int s1 = 1, s2 = 1;
         (void)fold(K, a.cnz, a.g.bc[4], a.g.bc[5], s1);
         (void)fold(K + ((zi & 1) ? 1 : -1), a.cnz, a.g.bc[4], a.g.bc[5], s2);
-        const T w1 = (T)(0.75 * s1), w2 = (T)(0.25 * s2);
 #pragma unroll
         for (int q = 0; q < TL::NPREC; ++q)
             if (q * FT + (int)threadIdx.x < TL::CN) {
-                const T v = w1 * p.c1[q] + w2 * p.c2[q];
+                const T v = lerp31(s1 < 0 ? -p.c1[q] : p.c1[q], s2 < 0 ? -p.c2[q] : p.c2[q]);
                 sc[zi & 1][q * FT + threadIdx.x] = G.cneg[q] ? -v : v;
             }
     };
@@ -366,9 +356,8 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
                 const int t0 = G.tap[q] & 0xffff;
                 const int tdx = ((G.tap[q] >> 16) & 1) ? 1 : -1;
                 const int tdy = ((G.tap[q] >> 17) & 1) ? TL::CX : -TL::CX;
-                const T w3 = (T)0.75, wq = (T)0.25;
                 const int t1 = t0 + tdy;
-                const T pe = w3 * (w3 * scp[t0] + wq * scp[t0 + tdx]) + wq * (w3 * scp[t1] + wq * scp[t1 + tdx]);
+                const T pe = lerp31(lerp31(scp[t0], scp[t0 + tdx]), lerp31(scp[t1], scp[t1 + tdx]));
                 if constexpr (XIN)
                     sx[buf][idx] = ((G.xneg[q] != (sz < 0)) ? -p.xs[q] : p.xs[q]) + pe;
                 else

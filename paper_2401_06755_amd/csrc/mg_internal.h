@@ -286,7 +286,7 @@ hipError_t launch_sweep2(int T_is_f64, int kt, int in_mode, int out_mode, const 
 // workgroup per 8^3 block of the level, for levels whose marching chain of
 // planes, not their bytes, sets the time.
 int block2_blocks(int nx, int ny, int nz);
-hipError_t launch_sweep2_block(int T_is_f64, int kt, int out_mode, const StencilArgs &a, hipStream_t s);
+hipError_t launch_sweep2_block(int T_is_f64, int kt, int in_mode, int out_mode, const StencilArgs &a, hipStream_t s);
 
 // ---- the coarsest level's FP64 inverse (mg_coarse.hip) ----
 struct CoarseArgs {
