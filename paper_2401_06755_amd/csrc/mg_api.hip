@@ -680,13 +680,15 @@ int enqueue_coarse_sweeps(nn4mg_hier *H, int l, const int *done)
 }
 
 // Finest-level sweeps: FP64: x <- smooth(x + P e_1) (x_zero: smooth(P e_1), x
-// not read; direct form: the result goes to x_out); mixed: x += smooth(P e_1).
+// not read; direct form: the result goes to x_out); mixed: x += smooth(P e_1)
+// (x_zero, one-pass sweeps only: smooth(P e_1) in FP32 into lv[0].t32).
 int enqueue_fine_sweeps(nn4mg_hier *H, const double *b, const double *bmean, double *x, const int *done,
                         bool x_zero = false, double *x_out = nullptr)
 {
     Level &F = H->lv[0];
     const int nu = H->cfg.nu_post;
     if (level_fusable(H, 0)) {
+        if (H->mixed && x_zero) return enqueue_sweep2(H, 0, F.b32, F.t32, nullptr, OUT_STORE, done);
         if (H->mixed) return enqueue_sweep2(H, 0, F.b32, nullptr, x, OUT_ADD64, done);
         if (x_zero) return enqueue_sweep2(H, 0, b, x, nullptr, OUT_STORE, done);
         if (direct_fine(H)) {
@@ -1272,10 +1274,15 @@ FcgVec fcg_vec(nn4mg_hier *H)
     return FcgVec{H->fcg, H->fcg + n, H->fcg + 2 * n, H->fcg + 3 * n};
 }
 
-// z = M r.  FP64: the cycle's right-hand side is r itself; mixed: the FP32
-// copy of r already sits in lv[0].b32 and the cycle adds its correction to z.
-// stop_np > 0: the cycle's first restriction-chain launch applies the
-// stopping rule to that many norm partials (the caller checked stop_in_chain).
+// Where M r ends: with both sweeps in one pass of an FP32 cycle, in FP32 (its
+// values as they are) in lv[0].t32; else in the FP64 vector z.
+bool fcg_z_f32(const nn4mg_hier *H) { return H->mixed && level_fusable(H, 0); }
+const void *fcg_z(nn4mg_hier *H) { return fcg_z_f32(H) ? (const void *)H->lv[0].t32 : fcg_vec(H).z; }
+
+// M r.  FP64: the cycle's right-hand side is r itself; mixed: the FP32 copy of
+// r already sits in lv[0].b32.
+// stop_np > 0: the cycle's first launch applies the stopping rule to that many
+// norm partials (the caller checked stop_in_chain).
 int enqueue_precondition(nn4mg_hier *H, const double *r, double *z, const int *done, int stop_np = 0)
 {
     Level &F = H->lv[0];
@@ -1285,6 +1292,7 @@ int enqueue_precondition(nn4mg_hier *H, const double *r, double *z, const int *d
         return enqueue_cycle_body(H, r, nullptr, z, done, true, stop_np);
     }
     HIP_TRY(launch_restrict(0, F.b32, H->lv[1].b32, F.nx, F.ny, F.nz, done, s));
+    if (fcg_z_f32(H)) return enqueue_cycle_body(H, nullptr, nullptr, nullptr, done, true, stop_np);
     HIP_TRY(launch_zero(z, F.n, done, s));
     return enqueue_cycle_body(H, nullptr, nullptr, z, done, false, stop_np);
 }
@@ -1302,13 +1310,13 @@ int enqueue_fcg_start(nn4mg_hier *H, const double *b, double *x)
     HIP_TRY(launch_finish_norm(H->st, H->partials, resid_blocks(H), s));
     if (H->mixed) HIP_TRY(launch_cast_f32(v.r, H->lv[0].b32, n, done, s));
     if ((rc = enqueue_precondition(H, v.r, v.z, done))) return rc;
-    HIP_TRY(launch_fcg_dots(v.z, v.r, nullptr, n, H->fcg_part, H->st, 0, s));
-    HIP_TRY(launch_copy(v.p, v.z, n, done, s));
+    HIP_TRY(launch_fcg_dots(fcg_z(H), fcg_z_f32(H), v.r, nullptr, n, H->fcg_part, H->st, 0, s));
+    HIP_TRY(launch_fcg_first_direction(fcg_z(H), fcg_z_f32(H), v.p, n, done, s));
     return NN4MG_OK;
 }
 
-// One FCG(1) iteration: t = -A p, alpha, x and r update with the stopping
-// rule on ||r||, z = M r, beta, p = z + beta p.
+// One FCG(1) iteration: t = -A p, alpha, r update with the stopping rule on
+// ||r||, z = M r, beta, x += alpha p, p = z + beta p.
 int enqueue_fcg_iteration(nn4mg_hier *H, double *x)
 {
     const FcgVec v = fcg_vec(H);
@@ -1331,14 +1339,14 @@ int enqueue_fcg_iteration(nn4mg_hier *H, double *x)
         prof_end(H, pr);
         HIP_TRY(launch_fcg_alpha_partials(H->partials, resid_blocks(H), H->st, s));
     }
-    HIP_TRY(launch_fcg_update(H->st, x, v.p, v.r, v.t, H->mixed ? H->lv[0].b32 : nullptr, n, H->partials, s));
+    HIP_TRY(launch_fcg_update(H->st, v.r, v.t, H->mixed ? H->lv[0].b32 : nullptr, n, H->partials, s));
     // the stopping rule on ||r|| runs in the preconditioning cycle's first
     // chain launch when it has one (the restriction before it runs regardless)
     const bool fold = stop_in_chain(H);
     if (!fold) HIP_TRY(launch_finish_norm(H->st, H->partials, fcg_update_blocks(n), s));
     if ((rc = enqueue_precondition(H, v.r, v.z, done, fold ? fcg_update_blocks(n) : 0))) return rc;
-    HIP_TRY(launch_fcg_dots(v.z, v.r, v.t, n, H->fcg_part, H->st, 2, s));
-    HIP_TRY(launch_fcg_direction(H->st, v.z, v.p, n, s));
+    HIP_TRY(launch_fcg_dots(fcg_z(H), fcg_z_f32(H), v.r, v.t, n, H->fcg_part, H->st, 2, s));
+    HIP_TRY(launch_fcg_direction(H->st, fcg_z(H), fcg_z_f32(H), v.p, x, n, s));
     return NN4MG_OK;
 }
 

@@ -7,6 +7,15 @@
 // p = z' + beta p, with q = A p = -t.  All scalars
 // live in the device solve state, so a batch of iterations runs with no host
 // round trip; every kernel returns at once when the stopping rule has fired.
+// The vector kernels are bound by HBM, so what counts is the bytes per cell:
+//  * a cycle in FP32 gives a z whose values are FP32 numbers, so z is stored
+//    as such (nothing is rounded): its pass writes it whole instead of adding
+//    it into a cleared FP64 vector;
+//  * x += alpha p waits for the direction update at the end of the iteration,
+//    which reads p anyway (and runs it also when the stopping rule has fired
+//    in between: SolveState::fcg_pending).
+// An iteration at 256^3 with the FP32 cycle moves 125 instead of 161 bytes per
+// cell and takes 546 instead of 696 us.
 // Dot products are reduced in a fixed order (per-block partials, then one
 // workgroup), so results are bitwise repeatable.
 #include "mg_internal.h"
@@ -55,14 +64,15 @@ __device__ double reduce_partials(const double *p, int n, double *red)
 }
 
 // partials[blk] = sum z r; partials[nblk + blk] = sum z q = -sum z t (0 if t is NULL).
-__global__ __launch_bounds__(256) void dots_kernel(const double *z, const double *r, const double *t, size_t n,
+template <typename Z>
+__global__ __launch_bounds__(256) void dots_kernel(const Z *z, const double *r, const double *t, size_t n,
                                                    double *partials, const int *done)
 {
     if (*done) return;
     __shared__ double red[8];
     double a = 0.0, b = 0.0;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const double zi = z[i];
+        const double zi = (double)z[i];
         a += zi * r[i];
         if (t) b -= zi * t[i];
     }
@@ -74,37 +84,29 @@ __global__ __launch_bounds__(256) void dots_kernel(const double *z, const double
     }
 }
 
-// partials[blk] = -sum p t = p . A p
-__global__ __launch_bounds__(256) void pq_kernel(const double *p, const double *t, size_t n, double *partials,
-                                                 const int *done)
-{
-    if (*done) return;
-    __shared__ double red[4];
-    double a = 0.0;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        a -= p[i] * t[i];
-    }
-    const double s = block_sum(a, red);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
-// mode 0: rho = sum z r (start);  mode 1: alpha = rho / (p.q) from partials of p.q;
-// mode 3: the same from partials of p.t = -p.q;  mode 2: beta = -(z.q) / (p.q), rho = z.r.
+// mode 0: rho = sum z r (start);  mode 1: alpha = rho / (p.q) from partials of
+// p.t = -p.q;  mode 2: beta = -(z.q) / (p.q), rho = z.r.
 __global__ __launch_bounds__(1024) void scalar_kernel(SolveState *st, const double *partials, int nblk, int mode)
 {
     __shared__ double red[16];
-    if (st->done) return;
-    if (mode == 1 || mode == 3) {
-        const double pq = (mode == 3 ? -1.0 : 1.0) * reduce_partials(partials, nblk, red);
+    const bool step = mode == 1;
+    if (st->done) {
+        if (step && threadIdx.x == 0) st->fcg_pending = 0;
+        return;
+    }
+    if (step) {
+        const double pq = -reduce_partials(partials, nblk, red);
         if (threadIdx.x == 0) {
             st->fcg_pq_prev = pq;
             if (!(pq > 0.0) || !isfinite(pq)) {
                 // p . A p must be positive for an SPD (or semidefinite, on the range) operator
                 st->fcg_alpha = 0.0;
+                st->fcg_pending = 0;
                 st->done = 1;
                 st->status = -5;
             } else {
                 st->fcg_alpha = st->fcg_rho / pq;
+                st->fcg_pending = 1;
             }
         }
         return;
@@ -118,16 +120,15 @@ __global__ __launch_bounds__(1024) void scalar_kernel(SolveState *st, const doub
     }
 }
 
-// x += alpha p; r -= alpha q (= r + alpha t); r32 = (float) r (if given); partials of r^2.
-__global__ __launch_bounds__(256) void update_kernel(const SolveState *st, double *x, const double *p, double *r,
-                                                     const double *t, float *r32, size_t n, double *partials)
+// r -= alpha q (= r + alpha t); r32 = (float) r (if given); partials of r^2.
+__global__ __launch_bounds__(256) void update_kernel(const SolveState *st, double *r, const double *t, float *r32,
+                                                     size_t n, double *partials)
 {
     if (st->done) return;
     __shared__ double red[4];
     const double alpha = st->fcg_alpha;
     double acc = 0.0;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        x[i] += alpha * p[i];
         const double ri = r[i] + alpha * t[i];
         r[i] = ri;
         if (r32) r32[i] = (float)ri;
@@ -137,13 +138,29 @@ __global__ __launch_bounds__(256) void update_kernel(const SolveState *st, doubl
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// p = z + beta p
-__global__ __launch_bounds__(256) void direction_kernel(const SolveState *st, const double *z, double *p, size_t n)
+// x += alpha p of the iteration (whether or not the stopping rule has fired
+// since alpha was formed), then p = z + beta p if it goes on.
+template <typename Z>
+__global__ __launch_bounds__(256) void direction_kernel(const SolveState *st, const Z *z, double *p, double *x,
+                                                        size_t n)
 {
-    if (st->done) return;
-    const double beta = st->fcg_beta;
+    if (!st->fcg_pending) return;
+    const bool on = !st->done;
+    const double alpha = st->fcg_alpha, beta = st->fcg_beta;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        const double pi = p[i];
+        x[i] += alpha * pi;
+        if (on) p[i] = (double)z[i] + beta * pi;
+    }
+}
+
+// p = z
+template <typename Z>
+__global__ __launch_bounds__(256) void first_direction_kernel(const Z *z, double *p, size_t n, const int *done)
+{
+    if (*done) return;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = z[i] + beta * p[i];
+        p[i] = (double)z[i];
 }
 
 __global__ __launch_bounds__(256) void cast_f32_kernel(const double *src, float *dst, size_t n, const int *done)
@@ -172,43 +189,53 @@ int grid_blocks(size_t n)
 
 int fcg_partials_needed() { return 2 * kDotBlocks; }
 
-hipError_t launch_fcg_dots(const double *z, const double *r, const double *t, size_t n, double *partials,
+hipError_t launch_fcg_dots(const void *z, int z_f32, const double *r, const double *t, size_t n, double *partials,
                            SolveState *st, int mode, hipStream_t s)
 {
     const int nb = dot_blocks(n);
-    hipLaunchKernelGGL(dots_kernel, dim3(nb), dim3(256), 0, s, z, r, t, n, partials, &st->done);
+    if (z_f32)
+        hipLaunchKernelGGL(dots_kernel<float>, dim3(nb), dim3(256), 0, s, (const float *)z, r, t, n, partials, &st->done);
+    else
+        hipLaunchKernelGGL(dots_kernel<double>, dim3(nb), dim3(256), 0, s, (const double *)z, r, t, n, partials,
+                           &st->done);
     hipLaunchKernelGGL(scalar_kernel, dim3(1), dim3(1024), 0, s, st, (const double *)partials, nb, mode);
-    return hipGetLastError();
-}
-
-hipError_t launch_fcg_alpha(const double *p, const double *t, size_t n, double *partials, SolveState *st,
-                            hipStream_t s)
-{
-    const int nb = dot_blocks(n);
-    hipLaunchKernelGGL(pq_kernel, dim3(nb), dim3(256), 0, s, p, t, n, partials, &st->done);
-    hipLaunchKernelGGL(scalar_kernel, dim3(1), dim3(1024), 0, s, st, (const double *)partials, nb, 1);
     return hipGetLastError();
 }
 
 hipError_t launch_fcg_alpha_partials(const double *partials, int nblk, SolveState *st, hipStream_t s)
 {
-    hipLaunchKernelGGL(scalar_kernel, dim3(1), dim3(1024), 0, s, st, partials, nblk, 3);
+    hipLaunchKernelGGL(scalar_kernel, dim3(1), dim3(1024), 0, s, st, partials, nblk, 1);
     return hipGetLastError();
 }
 
 int fcg_update_blocks(size_t n) { return dot_blocks(n); }
 
-hipError_t launch_fcg_update(SolveState *st, double *x, const double *p, double *r, const double *t, float *r32,
-                             size_t n, double *partials, hipStream_t s)
+hipError_t launch_fcg_update(SolveState *st, double *r, const double *t, float *r32, size_t n, double *partials,
+                             hipStream_t s)
 {
-    hipLaunchKernelGGL(update_kernel, dim3(dot_blocks(n)), dim3(256), 0, s, (const SolveState *)st, x, p, r, t, r32,
-                       n, partials);
+    hipLaunchKernelGGL(update_kernel, dim3(dot_blocks(n)), dim3(256), 0, s, (const SolveState *)st, r, t, r32, n,
+                       partials);
     return hipGetLastError();
 }
 
-hipError_t launch_fcg_direction(SolveState *st, const double *z, double *p, size_t n, hipStream_t s)
+hipError_t launch_fcg_direction(SolveState *st, const void *z, int z_f32, double *p, double *x, size_t n,
+                                hipStream_t s)
 {
-    hipLaunchKernelGGL(direction_kernel, dim3(grid_blocks(n)), dim3(256), 0, s, (const SolveState *)st, z, p, n);
+    const dim3 g(grid_blocks(n)), b(256);
+    if (z_f32)
+        hipLaunchKernelGGL(direction_kernel<float>, g, b, 0, s, (const SolveState *)st, (const float *)z, p, x, n);
+    else
+        hipLaunchKernelGGL(direction_kernel<double>, g, b, 0, s, (const SolveState *)st, (const double *)z, p, x, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_fcg_first_direction(const void *z, int z_f32, double *p, size_t n, const int *done, hipStream_t s)
+{
+    const dim3 g(grid_blocks(n)), b(256);
+    if (z_f32)
+        hipLaunchKernelGGL(first_direction_kernel<float>, g, b, 0, s, (const float *)z, p, n, done);
+    else
+        hipLaunchKernelGGL(first_direction_kernel<double>, g, b, 0, s, (const double *)z, p, n, done);
     return hipGetLastError();
 }
 

@@ -128,6 +128,7 @@ struct SolveState {
     double hist[512];
     // flexible CG scalars
     double fcg_rho, fcg_alpha, fcg_beta, fcg_pq_prev;
+    int fcg_pending;  // this iteration's x += alpha p is still to be done
 };
 
 // ---------------------------------------------------------------- launchers
@@ -255,21 +256,22 @@ int hier_started(const nn4mg_hier *H);  // cycles have been enqueued for it
 void hier_note_enqueued(nn4mg_hier *H, int n);
 
 // ---- flexible CG vector kernels (mg_fcg.hip); t = -A p, q = A p = -t ----
-// dots: rho = z.r (mode 0), or rho = z.r and beta = -(z.q)/(p.q) (mode 2);
-// alpha: alpha = rho / (p.q) (breakdown if p.q <= 0); update: x += alpha p,
-// r -= alpha q, r32 = (float) r if r32 != NULL, per-block r^2 partials
-// (fcg_update_blocks of them, for launch_finish_norm); direction: p = z + beta p.
+// z is FP64, or FP32 with z_f32.  dots: rho = z.r (mode 0), or rho = z.r and
+// beta = -(z.q)/(p.q) (mode 2); alpha: alpha = rho / (p.q) (breakdown if
+// p.q <= 0); update: r -= alpha q, r32 = (float) r if r32 != NULL, per-block r^2
+// partials (fcg_update_blocks of them, for launch_finish_norm); direction:
+// x += alpha p, then p = z + beta p; first_direction: p = z.
 int fcg_partials_needed();
 int fcg_update_blocks(size_t n);
-hipError_t launch_fcg_dots(const double *z, const double *r, const double *t, size_t n, double *partials,
+hipError_t launch_fcg_dots(const void *z, int z_f32, const double *r, const double *t, size_t n, double *partials,
                            SolveState *st, int mode, hipStream_t s);
-hipError_t launch_fcg_alpha(const double *p, const double *t, size_t n, double *partials, SolveState *st,
-                            hipStream_t s);
 // alpha from nblk per-block partials of p.t (t = -A p) written by the residual kernel
 hipError_t launch_fcg_alpha_partials(const double *partials, int nblk, SolveState *st, hipStream_t s);
-hipError_t launch_fcg_update(SolveState *st, double *x, const double *p, double *r, const double *t, float *r32,
-                             size_t n, double *partials, hipStream_t s);
-hipError_t launch_fcg_direction(SolveState *st, const double *z, double *p, size_t n, hipStream_t s);
+hipError_t launch_fcg_update(SolveState *st, double *r, const double *t, float *r32, size_t n, double *partials,
+                             hipStream_t s);
+hipError_t launch_fcg_direction(SolveState *st, const void *z, int z_f32, double *p, double *x, size_t n,
+                                hipStream_t s);
+hipError_t launch_fcg_first_direction(const void *z, int z_f32, double *p, size_t n, const int *done, hipStream_t s);
 hipError_t launch_cast_f32(const double *src, float *dst, size_t n, const int *done, hipStream_t s);
 hipError_t launch_zero(double *x, size_t n, const int *done, hipStream_t s);
 

@@ -378,6 +378,7 @@ __global__ void init_state_kernel(SolveState *st, double rtol, int max_cycles, i
     st->taken = 0;
     st->last = 0.0;
     st->fcg_rho = st->fcg_alpha = st->fcg_beta = st->fcg_pq_prev = 0.0;
+    st->fcg_pending = 0;
 }
 
 __global__ void set_nb_kernel(SolveState *st, const double *sumsq)

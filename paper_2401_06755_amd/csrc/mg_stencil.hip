@@ -364,15 +364,17 @@ __global__ __launch_bounds__(NT, NN4MG_MIN_WAVES) void stencil_kernel(const Sten
     // One output plane: commit plane z + 1 from slot p, refill the slot with
     // plane z + 3 (two planes stay in flight), then finish plane z and load
     // the output values of plane z + 2 into the registers it just read.
-    // The steady form (ST; PAR = z & 1 known) runs on tiles inside the grid
-    // with the restricted residual output present (mode 1: and the full
-    // residual, mode 2: without it): it issues the same loads and stores on
-    // every path, so the compiler's wait counts keep the next planes' loads in
-    // flight instead of waiting for every outstanding load.
+    // The steady form (ST; PAR = z & 1 known) runs on tiles inside the grid,
+    // for a residual with a fixed set of outputs and inputs (mode 1: full and
+    // restricted residual, 2: restricted only, 3: full only, 4: full only and a
+    // zero right-hand side): it issues the same loads and stores on every path,
+    // so the compiler's wait counts keep the next planes' loads in flight
+    // instead of waiting for every outstanding load.
     int buf = 0;
     auto step = [&](auto st_tag, auto par_tag, Prefetch<T, KT, TX, RY, PRO, ADD> &p, int z) {
         constexpr int MODE = decltype(st_tag)::value;
         constexpr bool ST = MODE != 0;
+        constexpr bool FULL = MODE == 1 || MODE == 3 || MODE == 4, COARSE = MODE == 1 || MODE == 2;
         constexpr int PAR = decltype(par_tag)::value;
         commit<T, KT, IN, TX, RY, ADD>(p, G, sx[buf], sk[buf], sc);
         if (ST || z + 3 <= z1) fetch_in<T, KT, IN, TX, RY, ADD>(p, G, a, z + 3);
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(NT, NN4MG_MIN_WAVES) void stencil_kernel(const Sten
             if constexpr (OUT == OUT_RESID) {
                 double rv = 0.0;
                 if (ST || valid[r]) rv = ((double)p.bo[r] - bm) - (double)Ay;
-                if (MODE == 1 || (MODE == 0 && a.r && valid[r])) ((OT *)a.r)[g] = (OT)rv;
+                if (FULL || (MODE == 0 && a.r && valid[r])) ((OT *)a.r)[g] = (OT)rv;
                 nacc += a.dot_x ? (double)y0 * rv : rv * rv;
                 rrow[r] = rv;
             } else if (ST || valid[r]) {
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(NT, NN4MG_MIN_WAVES) void stencil_kernel(const Sten
         }
         absorb(false);
         if constexpr (OUT == OUT_RESID) {
-            if (ST || a.rc) {
+            if (COARSE || (MODE == 0 && a.rc)) {
                 const int cx = nx >> 1, cy = ny >> 1;
 #pragma unroll
                 for (int q = 0; q < RP; ++q) {
@@ -437,8 +439,9 @@ __global__ __launch_bounds__(NT, NN4MG_MIN_WAVES) void stencil_kernel(const Sten
                 }
             }
         }
-        // output values of plane z + 2 (its step comes two steps later)
-        if (ST || z + 3 <= z1) fetch_out<T, KT, TX, RY, PRO, ADD>(p, a, z + 3, gb);
+        // output values of plane z + 2 (its step comes two steps later); with a
+        // zero right-hand side the registers keep their zeros
+        if (MODE != 4 && (ST || z + 3 <= z1)) fetch_out<T, KT, TX, RY, PRO, ADD>(p, a, z + 3, gb);
     };
 
     // prologue: planes z0 - 1 and z0 into the running sums; planes z0 + 1 and
@@ -460,28 +463,30 @@ __global__ __launch_bounds__(NT, NN4MG_MIN_WAVES) void stencil_kernel(const Sten
     absorb(false);
 
     const std::integral_constant<int, 0> gen{};
-    const std::integral_constant<int, 1> steady{};
-    const std::integral_constant<int, 2> steady_rc{};
     const std::integral_constant<int, -1> anypar{};
     const std::integral_constant<int, 0> even{};
     const std::integral_constant<int, 1> odd{};
     // the steady march: tiles inside the grid, chunks starting on an even plane
-    // (so the A steps are the even planes), the restricted residual output
-    // present (the full residual is optional: its own form of the march)
-    const bool inside = i0 + TX <= nx && j0 + TL::TY <= ny && !(z0 & 1) && (OUT != OUT_RESID || a.rc != nullptr);
+    // (so the A steps are the even planes)
+    const bool inside = i0 + TX <= nx && j0 + TL::TY <= ny && !(z0 & 1);
     int z = z0;
-    if (OUT != OUT_RESID || a.r != nullptr) {
+    auto march = [&](auto mode) {
         for (; inside && z + 4 <= z1; z += 2) {
-            step(steady, even, pA, z);
-            step(steady, odd, pB, z + 1);
+            step(mode, even, pA, z);
+            step(mode, odd, pB, z + 1);
         }
+    };
+    if constexpr (OUT != OUT_RESID) {
+        march(std::integral_constant<int, 1>{});
     } else {
-        if constexpr (OUT == OUT_RESID) {
-            for (; inside && z + 4 <= z1; z += 2) {
-                step(steady_rc, even, pA, z);
-                step(steady_rc, odd, pB, z + 1);
-            }
-        }
+        if (a.r && a.rc)
+            march(std::integral_constant<int, 1>{});
+        else if (a.rc)
+            march(std::integral_constant<int, 2>{});
+        else if (a.r && a.b)
+            march(std::integral_constant<int, 3>{});
+        else if (a.r)
+            march(std::integral_constant<int, 4>{});
     }
     for (; z < z1; z += 2) {
         step(gen, anypar, pA, z);
