@@ -9,12 +9,10 @@
 // products of the 1D linear-element vectors
 //     M = h [1, 4, 1] / 6 (mass),  G = [-1, 0, 1] / 2 (first derivative),
 //     K = [-1, 2, -1] / h (stiffness),
-// so each is evaluated separably on a 27-value neighbourhood held in
-// registers.  One thread owns one cell; the neighbourhoods of adjacent threads
-// overlap in L1/L2, which carries the re-reads (the momentum predictor, with
-// twelve fields the heaviest, stages its planes in LDS instead).  This explicit part moves
-// about a kilobyte per cell per step; the three pressure solves, run by the
-// multigrid hierarchy of this library with a fixed cycle count, dominate.
+// evaluated separably: the linear filters by a z-march over LDS-staged planes
+// (mg_step_linear.hip), the quadratic ones (5x5x5) here, in 8^3 blocks staged in
+// LDS.  The three pressure solves, run by the multigrid hierarchy of this
+// library with a fixed cycle count, take most of a step.
 //
 // Boundary rules on the tank box (Sec. 3.1: free-slip side and bottom walls,
 // an outlet with zero pressure on top):
@@ -35,7 +33,7 @@
 // physical Laplace jump across a drop and gradient -s_t, so s_t enters the
 // predictor as +f(s_t; w_m).
 #include "mg_async.h"
-#include "mg_internal.h"
+#include "mg_step.h"
 
 #include <cmath>
 #include <cstring>
@@ -45,192 +43,16 @@ using namespace nn4mg;
 
 namespace {
 
-struct Grid {
-    int nx, ny, nz;
-    double h;
-    size_t n;
-};
-
-// Face bits of a boundary rule: bit f set = -mirror on face f
-// (xlo, xhi, ylo, yhi, zlo, zhi); clear = +mirror.
-constexpr unsigned kEven = 0u;
-constexpr unsigned kOddTop = 32u;  // p_nh, its increment, p_hs above
-__host__ __device__ constexpr unsigned rule_vel(int d) { return d == 0 ? 3u : (d == 1 ? 12u : 16u); }
-__host__ __device__ constexpr unsigned rule_grad(int d) { return 3u << (2 * d); }
-
 __device__ inline size_t at(const Grid &g, int i, int j, int k)
 {
     return (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * (size_t)k);
 }
 
-// Value of the padded field at (i, j, k), each index at most one cell outside.
-__device__ inline double tap(const double *u, unsigned odd, const Grid &g, int i, int j, int k)
-{
-    double s = 1.0;
-    if (i < 0) {
-        i = 0;
-        if (odd & 1u) s = -s;
-    } else if (i >= g.nx) {
-        i = g.nx - 1;
-        if (odd & 2u) s = -s;
-    }
-    if (j < 0) {
-        j = 0;
-        if (odd & 4u) s = -s;
-    } else if (j >= g.ny) {
-        j = g.ny - 1;
-        if (odd & 8u) s = -s;
-    }
-    if (k < 0) {
-        k = 0;
-        if (odd & 16u) s = -s;
-    } else if (k >= g.nz) {
-        k = g.nz - 1;
-        if (odd & 32u) s = -s;
-    }
-    return s * u[at(g, i, j, k)];
-}
-
-// 27 values around a cell: v[(c+1)*9 + (b+1)*3 + (a+1)] at (i+a, j+b, k+c).
-struct Nb {
-    double v[27];
-    __device__ double mid() const { return v[13]; }
-};
-
-__device__ inline void load(Nb &n, const double *u, unsigned odd, const Grid &g, int i, int j, int k)
-{
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-#pragma unroll
-        for (int b = 0; b < 3; ++b)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) n.v[c * 9 + b * 3 + a] = tap(u, odd, g, i + a - 1, j + b - 1, k + c - 1);
-}
-
-struct V3 {
-    double m, z, p;  // weights at offsets -1, 0, +1
-};
-
-// f(u; X (x) Y (x) Z), X along i.
-__device__ inline double sep(const Nb &n, const V3 &X, const V3 &Y, const V3 &Z)
-{
-    double out = 0.0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double pl = 0.0;
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const double *r = &n.v[c * 9 + b * 3];
-            const double row = X.m * r[0] + X.z * r[1] + X.p * r[2];
-            pl += (b == 0 ? Y.m : (b == 1 ? Y.z : Y.p)) * row;
-        }
-        out += (c == 0 ? Z.m : (c == 1 ? Z.z : Z.p)) * pl;
-    }
-    return out;
-}
-
-// f(k C; X (x) Y (x) Z) with the products formed on the fly (no third neighbourhood).
-__device__ inline double sepp(const Nb &k, const Nb &n, const V3 &X, const V3 &Y, const V3 &Z)
-{
-    double out = 0.0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double pl = 0.0;
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const double *r = &n.v[c * 9 + b * 3];
-            const double *kr = &k.v[c * 9 + b * 3];
-            const double row = X.m * (kr[0] * r[0]) + X.z * (kr[1] * r[1]) + X.p * (kr[2] * r[2]);
-            pl += (b == 0 ? Y.m : (b == 1 ? Y.z : Y.p)) * row;
-        }
-        out += (c == 0 ? Z.m : (c == 1 ? Z.z : Z.p)) * pl;
-    }
-    return out;
-}
-
-struct Filt {
-    V3 M, G, K, m;  // m = M / h
-    double ml;      // lumped mass h^3
-    __device__ explicit Filt(double h)
-    {
-        M = {h / 6.0, 4.0 * h / 6.0, h / 6.0};
-        G = {-0.5, 0.0, 0.5};
-        K = {-1.0 / h, 2.0 / h, -1.0 / h};
-        m = {1.0 / 6.0, 4.0 / 6.0, 1.0 / 6.0};
-        ml = h * h * h;
-    }
-    // w_d = G along d, M across (the printed w_x of Sec. 2.2.3 for d = 0)
-    __device__ double d(const Nb &n, int dir) const
-    {
-        return dir == 0 ? sep(n, G, M, M) : (dir == 1 ? sep(n, M, G, M) : sep(n, M, M, G));
-    }
-    // w_dd^PG = K along d, M across
-    __device__ double pg(const Nb &n, int dir) const
-    {
-        return dir == 0 ? sep(n, K, M, M) : (dir == 1 ? sep(n, M, K, M) : sep(n, M, M, K));
-    }
-    __device__ double lap(const Nb &n) const { return sep(n, K, M, M) + sep(n, M, K, M) + sep(n, M, M, K); }
-    __device__ double mass(const Nb &n) const { return sep(n, M, M, M); }
-    // w_m / m_l - E: the residual filter of Eq. a_psi
-    __device__ double mass_resid(const Nb &n) const { return sep(n, m, m, m) - n.mid(); }
-};
-
-// Eq. k-Txx: 1/2 [f(k C; w) + k f(C; w) - C f(k; w)] with the product of the
-// padded values as the halo of k C.  which: 0..2 = w_dd^PG, 3 = w_lap.
-__device__ inline double fdiff(const Filt &F, const Nb &Cn, const Nb &kn, int which)
-{
-    double fk;  // f(k C; w)
-    if (which == 3)
-        fk = sepp(kn, Cn, F.K, F.M, F.M) + sepp(kn, Cn, F.M, F.K, F.M) + sepp(kn, Cn, F.M, F.M, F.K);
-    else if (which == 0)
-        fk = sepp(kn, Cn, F.K, F.M, F.M);
-    else if (which == 1)
-        fk = sepp(kn, Cn, F.M, F.K, F.M);
-    else
-        fk = sepp(kn, Cn, F.M, F.M, F.K);
-    if (which == 3) return 0.5 * (fk + kn.mid() * F.lap(Cn) - Cn.mid() * F.lap(kn));
-    return 0.5 * (fk + kn.mid() * F.pg(Cn, which) - Cn.mid() * F.pg(kn, which));
-}
-
-struct Phys {
-    double rho_l, rho_g, mu_l, mu_g, g, sigma, dt;
-};
-
-template <typename F>
-__device__ inline bool cell_of(const Grid &g, F &&body)
-{
-    const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= g.n) return false;
-    const int i = (int)(id % (size_t)g.nx);
-    const size_t t = id / (size_t)g.nx;
-    body(id, i, (int)(t % (size_t)g.ny), (int)(t / (size_t)g.ny));
-    return true;
-}
-
-struct F3 {
-    double *p[3];
-};
-struct C3 {
-    const double *p[3];
-};
-
 // ------------------------------------------------------------------ kernels
 
-// ---- one workgroup per 8^3 block ----
-// For kernels that filter several fields per cell (the advection and the PG
-// diffusivity of the three components) each field is staged once in LDS on
-// the block plus a one-cell halo (10^3 cells, the field's boundary rule
-// applied as tap() applies it), and each thread gathers its cell's 27 values
-// from there into an Nb: the values load() gives, with one global load per
-// staged cell instead of 27 per cell.  Two staging buffers alternate, one
-// barrier per field: a thread stages field f only after the barrier of field
-// f - 1, which every thread reaches after gathering f - 2.  (For the kernels
-// that filter one or two fields, and the plane-marching momentum kernel, the
-// per-cell gathers through L1/L2 measured faster.)
+// ---- one workgroup per 8^3 block (the quadratic kernels) ----
 constexpr int SB = 8;                // block edge
 constexpr int SBT = SB * SB * SB;    // threads: one cell each
-constexpr int SL = SB + 2;           // staged edge
-constexpr int SLN = SL * SL * SL;    // staged cells
 
 // This thread's cell of the workgroup's block (the block at (i0, j0, k0)); a
 // ragged block's threads beyond the grid work on their cell clamped into it
@@ -262,397 +84,12 @@ unsigned blocks_of(const Grid &g)
     return (unsigned)(((g.nx + SB - 1) / SB) * ((g.ny + SB - 1) / SB) * ((g.nz + SB - 1) / SB));
 }
 
-// Neighbourhoods from LDS: load_nb(nb, u, odd) stages field u (rule odd) into
-// the next buffer, waits for the workgroup and gathers this thread's 27 values.
-struct LNb {
-    double (*buf)[SLN];
-    const Grid &g;
-    const BCell &X;
-    int next;
-    template <typename V>
-    __device__ void stage_gather(Nb &n, const V &val)
-    {
-        double *b = buf[next];
-        next ^= 1;
-        const int t = threadIdx.x;
-#pragma unroll
-        for (int r = 0; r < (SLN + SBT - 1) / SBT; ++r) {
-            const int idx = t + r * SBT;
-            if (idx < SLN) {
-                const int x = idx % SL, y = (idx / SL) % SL, z = idx / (SL * SL);
-                b[idx] = val(X.i0 + x - 1, X.j0 + y - 1, X.k0 + z - 1);
-            }
-        }
-        __syncthreads();
-        const int tx = t % SB, ty = (t / SB) % SB, tz = t / (SB * SB);
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-            for (int bb = 0; bb < 3; ++bb)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) n.v[c * 9 + bb * 3 + a] = b[(tx + a) + SL * ((ty + bb) + SL * (tz + c))];
-    }
-    __device__ void operator()(Nb &n, const double *u, unsigned odd)
-    {
-        const Grid &gg = g;
-        stage_gather(n, [&](int i, int j, int k) { return tap(u, odd, gg, i, j, k); });
-    }
-};
-
-// rho, mu (Eq. rho), grad C in derivative units, unit normals.
-__global__ __launch_bounds__(256) void props_kernel(Grid g, Phys P, const double *C, double *rho, double *mu, F3 Cd,
-                                                    F3 nrm)
-{
-    cell_of(g, [&](size_t id, int i, int j, int k) {
-        const Filt F(g.h);
-        Nb c;
-        load(c, C, kEven, g, i, j, k);
-        const double c0 = c.mid();
-        rho[id] = P.rho_l * c0 + P.rho_g * (1.0 - c0);
-        mu[id] = P.mu_l * c0 + P.mu_g * (1.0 - c0);
-        double gd[3];
-        for (int d = 0; d < 3; ++d) gd[d] = F.d(c, d) / F.ml;
-        const double l = sqrt(gd[0] * gd[0] + gd[1] * gd[1] + gd[2] * gd[2]);
-        const double eps = 1e-7 / g.h;
-        for (int d = 0; d < 3; ++d) {
-            Cd.p[d][id] = gd[d];
-            nrm.p[d][id] = gd[d] / (eps + l);
-        }
-    });
-}
-
-// Curvature kappa = div n (Eq. curvature) and the surface-tension force
-// sigma kappa grad C (Eq. surface-tension-k).
-__global__ __launch_bounds__(256) void surface_kernel(Grid g, double sigma, C3 nrm, C3 Cd, F3 st)
-{
-    cell_of(g, [&](size_t id, int i, int j, int k) {
-        const Filt F(g.h);
-        double kap = 0.0;
-        for (int d = 0; d < 3; ++d) {
-            Nb n;
-            load(n, nrm.p[d], rule_grad(d), g, i, j, k);
-            kap += F.d(n, d);
-        }
-        kap /= F.ml;
-        for (int d = 0; d < 3; ++d) st.p[d][id] = sigma * kap * Cd.p[d][id];
-    });
-}
-
-// Right-hand side of Eq. ph_disc: sum_d f(s_t,d; w_d) + f(g rho; w_z), minus
-// the Laplacian filter applied to the affine part of p_hs's bottom halo, so the
-// solve sees homogeneous rules.
-__global__ __launch_bounds__(256) void rhs_hydrostatic_kernel(Grid g, double grav, C3 st, const double *rho,
-                                                              double *b)
-{
-    cell_of(g, [&](size_t id, int i, int j, int k) {
-        const Filt F(g.h);
-        double s = 0.0;
-        for (int d = 0; d < 3; ++d) {
-            Nb n;
-            load(n, st.p[d], rule_grad(d), g, i, j, k);
-            s += F.d(n, d);
-        }
-        Nb r, lift;
-        load(r, rho, kEven, g, i, j, k);
-        // the halo plane below k = 0 carries g h rho(i, j, 0); everything else is zero
-        const double gh = grav * g.h;
-        for (int q = 0; q < 27; ++q) lift.v[q] = (k == 0 && q < 9) ? gh * r.v[q] : 0.0;
-        for (int q = 0; q < 27; ++q) r.v[q] *= grav;
-        s += F.d(r, 2);
-        if (k == 0) s -= F.lap(lift);
-        b[id] = s;
-    });
-}
-
-// Advection of each velocity component by the iterate: adv_c = q . grad q_c.
-__global__ __launch_bounds__(SBT) void advection_kernel(Grid g, C3 q, F3 adv)
-{
-    __shared__ double sb[2][SLN];
-    const BCell X = bcell(g);
-    LNb load_nb{sb, g, X, 0};
-    const Filt F(g.h);
-    const size_t id = X.id;
-    const double q0[3] = {q.p[0][id], q.p[1][id], q.p[2][id]};
-    for (int c = 0; c < 3; ++c) {
-        Nb n;
-        load_nb(n, q.p[c], rule_vel(c));
-        double a = 0.0;
-        for (int d = 0; d < 3; ++d) a += q0[d] * (F.d(n, d) / F.ml);
-        if (X.valid) adv.p[c][id] = a;
-    }
-}
-
-// Isotropic Petrov-Galerkin diffusivity of each component (Eq. k_Psi-n with
-// Eqs. efficient-kabs-special-case, k-square with h_Psi = h, max-k and the
-// residual a_Psi of Eq. a_psi, alpha_a = 2): k_c = rho min(k_max, k_abs, k_sq) + mu.
-__global__ __launch_bounds__(SBT) void pg_velocity_kernel(Grid g, C3 q, C3 adv, const double *rho,
-                                                          const double *mu, F3 kq)
-{
-    __shared__ double sb[2][SLN];
-    const BCell X = bcell(g);
-    LNb load_nb{sb, g, X, 0};
-    const Filt F(g.h);
-    const size_t id = X.id;
-    const double eps_k = 1e-7, a_kabs = 1.0 / 16.0, a_ksq = 4.0, h = g.h;
-    const double u = q.p[0][id], v = q.p[1][id], w = q.p[2][id];
-    for (int c = 0; c < 3; ++c) {
-        Nb n;
-        load_nb(n, q.p[c], rule_vel(c));
-        const double px = F.d(n, 0) / F.ml, py = F.d(n, 1) / F.ml, pz = F.d(n, 2) / F.ml;
-        Nb an;
-        load_nb(an, adv.p[c], kEven);
-        const double a = 2.0 * F.mass_resid(an);
-        const double G = fabs(px) + fabs(py) + fabs(pz);
-        const double kabs = a_kabs * h * fabs(a) / (eps_k + G / 3.0);
-        const double g2 = px * px + py * py + pz * pz;
-        const double advabs = fabs(u * px) + fabs(v * py) + fabs(w * pz);
-        const double ksq = a_ksq * a * a * h / (eps_k + advabs / 3.0 * g2);
-        const double kmax = h * (fabs(u) + fabs(v) + fabs(w));
-        const double m = fmin(kmax, fmin(kabs, ksq));
-        if (X.valid) kq.p[c][id] = rho[id] * m + mu[id];
-    }
-}
-
-// One predictor iteration (Eqs. Petrov, velocity-1): the momentum residual
-// s_c = rho m_l adv_c + f_lap(q_c, k_c) + f(p_hs + p_nh; w_c) - f(s_t,c; w_m)
-// [- f(-g rho; w_m) for c = z] gives q~_c = (-s_c / m_l + rho q^n_c / dt) / (rho / dt),
-// and the next iterate is (q^n + q~) / 2.
-// Its twelve input fields are staged in LDS: one workgroup owns an MT_X x MT_Y
-// column of cells and marches MT_Z planes; each plane of every field is loaded
-// once, with its halo rule (and the lifted bottom halo of p_hs), into a
-// three-plane rotation, and each cell's 27-value neighbourhoods are gathered
-// from LDS in the order load() builds them (the same arithmetic as the
-// per-cell form).  The neighbourhood re-reads that would go through L1/L2
-// (324 loads per cell) become LDS reads.
-constexpr int MT_X = 16, MT_Y = 8, MT_Z = 8;
-constexpr int MP_X = MT_X + 2, MP_N = (MT_X + 2) * (MT_Y + 2);
-constexpr int M_NF = 12;  // p_hs, p_nh, rho, q0..2, kq0..2, st0..2
-
-struct MomIn {
-    const double *u[M_NF];
-};
-
-__device__ inline unsigned mom_rule(int f)
-{
-    return f <= 1 ? kOddTop : (f == 2 ? kEven : (f <= 5 ? rule_vel(f - 3) : (f <= 8 ? kEven : rule_grad(f - 9))));
-}
-
-__device__ inline void gather(Nb &n, const double *sf, const int (&slot)[3], int li, int lj)
-{
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double *pl = sf + slot[c] * MP_N;
-#pragma unroll
-        for (int b = 0; b < 3; ++b)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) n.v[c * 9 + b * 3 + a] = pl[(lj + b) * MP_X + (li + a)];
-    }
-}
-
-__global__ __launch_bounds__(MT_X * MT_Y) void momentum_lds_kernel(Grid g, Phys P, C3 qn, MomIn in, C3 adv,
-                                                                   F3 qt, F3 qnext)
-{
-    __shared__ double sm[M_NF][3][MP_N];
-    const int tx = (g.nx + MT_X - 1) / MT_X, ty = (g.ny + MT_Y - 1) / MT_Y;
-    const int bx = blockIdx.x % tx, rest = blockIdx.x / tx;
-    const int by = rest % ty, bz = rest / ty;
-    const int i0 = bx * MT_X, j0 = by * MT_Y, z0 = bz * MT_Z;
-    const int z1 = min(z0 + MT_Z, g.nz);
-    const int li = threadIdx.x % MT_X, lj = threadIdx.x / MT_X;
-    const int i = i0 + li, j = j0 + lj;
-    const bool valid = i < g.nx && j < g.ny;
-    const double gh = P.g * g.h;
-
-    // plane z of every field into slot (z + 3) % 3: clamped addresses and the
-    // faces crossed first, then every load in flight, then the signs of each
-    // field's rule (the product over the crossed faces, as tap() forms it)
-    constexpr int NR = (MP_N + MT_X * MT_Y - 1) / (MT_X * MT_Y);
-    auto stage = [&](int z) {
-        const int sl = (z + 3) % 3;
-        const int zc = z < 0 ? 0 : (z >= g.nz ? g.nz - 1 : z);
-        const unsigned zbit = z < 0 ? 16u : (z >= g.nz ? 32u : 0u);
-        size_t off[NR];
-        unsigned bits[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int c = min((int)threadIdx.x + r * MT_X * MT_Y, MP_N - 1);
-            const int py = c / MP_X, px = c - py * MP_X;
-            const int gi = i0 + px - 1, gj = j0 + py - 1;
-            const int ci = gi < 0 ? 0 : (gi >= g.nx ? g.nx - 1 : gi);
-            const int cj = gj < 0 ? 0 : (gj >= g.ny ? g.ny - 1 : gj);
-            bits[r] = zbit | (gi < 0 ? 1u : (gi >= g.nx ? 2u : 0u)) | (gj < 0 ? 4u : (gj >= g.ny ? 8u : 0u));
-            off[r] = at(g, ci, cj, zc);
-        }
-        double v[M_NF][NR];
-#pragma unroll
-        for (int f = 0; f < M_NF; ++f)
-#pragma unroll
-            for (int r = 0; r < NR; ++r) v[f][r] = in.u[f][off[r]];
-#pragma unroll
-        for (int f = 0; f < M_NF; ++f) {
-            const unsigned rule = mom_rule(f);
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const int c = (int)threadIdx.x + r * MT_X * MT_Y;
-                if (c < MP_N) {
-                    double x = (__popc(bits[r] & rule) & 1) ? -v[f][r] : v[f][r];
-                    if (f == 0 && z == -1) x += gh * v[2][r];  // lifted bottom halo of p_hs (rho +mirror)
-                    sm[f][sl][c] = x;
-                }
-            }
-        }
-    };
-    stage(z0 - 1);
-    stage(z0);
-    for (int k = z0; k < z1; ++k) {
-        stage(k + 1);
-        __syncthreads();
-        const int slot[3] = {(k + 2) % 3, k % 3, (k + 1) % 3};  // planes k - 1, k, k + 1
-        if (valid) {
-            const size_t id = at(g, i, j, k);
-            const Filt F(g.h);
-            const double r0 = in.u[2][id];
-            double ghs[3], gnh[3], buoy;
-            {
-                Nb p;
-                gather(p, &sm[0][0][0], slot, li, lj);
-                for (int c = 0; c < 3; ++c) ghs[c] = F.d(p, c);
-            }
-            {
-                Nb p;
-                gather(p, &sm[1][0][0], slot, li, lj);
-                for (int c = 0; c < 3; ++c) gnh[c] = F.d(p, c);
-            }
-            {
-                Nb r;
-                gather(r, &sm[2][0][0], slot, li, lj);
-                for (int e = 0; e < 27; ++e) r.v[e] *= -P.g;
-                buoy = F.mass(r);
-            }
-            for (int c = 0; c < 3; ++c) {
-                double s;
-                {
-                    Nb qv, kv;
-                    gather(qv, &sm[3 + c][0][0], slot, li, lj);
-                    gather(kv, &sm[6 + c][0][0], slot, li, lj);
-                    s = fdiff(F, qv, kv, 3);
-                }
-                s += ghs[c];
-                s += gnh[c];
-                {   // surface tension with the sign the Stage-1 pressure balances
-                    Nb t;
-                    gather(t, &sm[9 + c][0][0], slot, li, lj);
-                    s += F.mass(t);
-                }
-                if (c == 2) s -= buoy;
-                s += r0 * F.ml * adv.p[c][id];
-                const double qnc = qn.p[c][id];
-                const double t = (-s / F.ml + r0 * qnc / P.dt) / (r0 / P.dt);
-                qt.p[c][id] = t;
-                qnext.p[c][id] = 0.5 * (qnc + t);
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// Right-hand side of Eq. ph_disc2 for the pressure increment:
-// -(1/dt) sum_d f(rho q~_d; w_d) + (1/dt) sum_d q~_d f(rho; w_d).
-__global__ __launch_bounds__(256) void rhs_nonhydrostatic_kernel(Grid g, double dt, C3 qt, const double *rho,
-                                                                 double *b)
-{
-    cell_of(g, [&](size_t id, int i, int j, int k) {
-        const Filt F(g.h);
-        Nb r;
-        load(r, rho, kEven, g, i, j, k);
-        double s = 0.0;
-        for (int d = 0; d < 3; ++d) {
-            Nb m;
-            load(m, qt.p[d], rule_vel(d), g, i, j, k);
-            for (int e = 0; e < 27; ++e) m.v[e] *= r.v[e];
-            s -= F.d(m, d) / dt;
-            s += qt.p[d][id] * F.d(r, d) / dt;
-        }
-        b[id] = s;
-    });
-}
-
-// Eq. vel-cor: q~_d -= dt f(dp; w_d) / (m_l rho); p_nh += dp.
-__global__ __launch_bounds__(256) void correct_kernel(Grid g, double dt, const double *dp, const double *rho, C3 qin,
-                                                      F3 qout, double *p_nh)
-{
-    cell_of(g, [&](size_t id, int i, int j, int k) {
-        const Filt F(g.h);
-        Nb n;
-        load(n, dp, kOddTop, g, i, j, k);
-        const double r0 = rho[id];
-        for (int d = 0; d < 3; ++d) qout.p[d][id] = qin.p[d][id] + -dt * (F.d(n, d) / F.ml) / r0;
-        p_nh[id] += n.mid();
-    });
-}
-
 // u . grad C with the new velocity (input of the residual of Eq. a_psi for C).
 __global__ __launch_bounds__(256) void advection_c_kernel(Grid g, C3 q, C3 Cd, double *out)
 {
-    cell_of(g, [&](size_t id, int, int, int) {
-        out[id] = q.p[0][id] * Cd.p[0][id] + q.p[1][id] * Cd.p[1][id] + q.p[2][id] * Cd.p[2][id];
-    });
-}
-
-// Anisotropic compressive diffusivities of the volume fraction (Sec. 2.3.5):
-// linear interface detectors S_d, weights w+ and w-, k+ = 3 k_abs and the
-// negative (compressive) k- of Eq. negativek with its normalisation, clamped
-// to [-alpha_min h^2 / dt, alpha_max h^2 / dt] (Eq. alpha_min_and_max).
-__global__ __launch_bounds__(256) void pg_volume_fraction_kernel(Grid g, double dt, const double *C, C3 Cd, C3 q,
-                                                                 const double *advc, F3 kd)
-{
-    cell_of(g, [&](size_t id, int i, int j, int k) {
-        const Filt F(g.h);
-        const double Kp = 300.0, Km = 300.0, beta = 0.1, eps_x = 1e-4, Kpos = 3.0, eps_k = 1e-7, h = g.h;
-        const double kmin = 1e-4 / dt * h * h, kclamp = 0.05 / dt * h * h;
-        Nb an;
-        load(an, advc, kEven, g, i, j, k);
-        const double a = 2.0 * F.mass_resid(an);
-        const double c0 = C[id];
-        double S[3];
-        S[0] = (c0 - tap(C, kEven, g, i - 1, j, k)) * (tap(C, kEven, g, i + 1, j, k) - c0);
-        S[1] = (c0 - tap(C, kEven, g, i, j - 1, k)) * (tap(C, kEven, g, i, j + 1, k) - c0);
-        S[2] = (c0 - tap(C, kEven, g, i, j, k - 1)) * (tap(C, kEven, g, i, j, k + 1) - c0);
-        if (c0 > 0.95 || c0 < 0.05) S[0] = S[1] = S[2] = -1.0;
-        const double cx = Cd.p[0][id], cy = Cd.p[1][id], cz = Cd.p[2][id];
-        const double u = q.p[0][id], v = q.p[1][id], w = q.p[2][id];
-        const double g2 = cx * cx + cy * cy + cz * cz;
-        const double proj = (u * cx + v * cy + w * cz) / (eps_x + g2);
-        const double us = cx * proj, vs = cy * proj, ws = cz * proj;
-        const double kneg = -beta * (u * u + v * v + w * w) / (eps_x + g2 * (fabs(us) + fabs(vs) + fabs(ws)) / 3.0);
-        const double G = fabs(cx) + fabs(cy) + fabs(cz);
-        const double kabs = (1.0 / 16.0) * h * fabs(a) / (eps_k + G / 3.0);
-        for (int d = 0; d < 3; ++d) {
-            const double wp = -fmax(-1.0, fmin(0.0, Kp * S[d]));
-            const double wm = fmin(1.0, fmax(0.0, Km * S[d]));
-            const double kk = wp * (Kpos * kabs) + wm * (kneg / h);
-            kd.p[d][id] = fmax(-kmin, fmin(kclamp, kk));
-        }
-    });
-}
-
-// Eqs. Petrov-C, transport-indicator-1: C^{n+1} = C - dt s_C / m_l with
-// s_C = m_l u . grad C + sum_d f_d(C, k_d; w_dd^PG).
-__global__ __launch_bounds__(256) void volume_fraction_kernel(Grid g, double dt, const double *C, C3 kd, C3 q, C3 Cd,
-                                                              double *Cnew)
-{
-    cell_of(g, [&](size_t id, int i, int j, int k) {
-        const Filt F(g.h);
-        double s = F.ml * (q.p[0][id] * Cd.p[0][id] + q.p[1][id] * Cd.p[1][id] + q.p[2][id] * Cd.p[2][id]);
-        Nb cn;
-        load(cn, C, kEven, g, i, j, k);
-        for (int d = 0; d < 3; ++d) {
-            Nb kn;
-            load(kn, kd.p[d], kEven, g, i, j, k);
-            s += fdiff(F, cn, kn, d);
-        }
-        Cnew[id] = cn.mid() - dt * s / F.ml;
-    });
+    const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= g.n) return;
+    out[id] = q.p[0][id] * Cd.p[0][id] + q.p[1][id] * Cd.p[1][id] + q.p[2][id] * Cd.p[2][id];
 }
 
 __global__ __launch_bounds__(256) void copy3_kernel(size_t n, C3 src, F3 dst)
@@ -1229,11 +666,6 @@ int hip_fail(hipError_t e, const char *what)
     } while (0)
 
 dim3 cells_grid(const Grid &g) { return dim3((unsigned)((g.n + 255) / 256)); }
-dim3 mom_grid(const Grid &g)
-{
-    return dim3((unsigned)(((g.nx + MT_X - 1) / MT_X) * ((g.ny + MT_Y - 1) / MT_Y) * ((g.nz + MT_Z - 1) / MT_Z)));
-}
-
 // Fixed-cycle solve of A x = b on the pressure hierarchy; the work pair
 // (b, px) is the same for every solve, so a captured cycle stays valid.  The
 // solve is enqueued with nothing waited for on the host (its status, residual
@@ -1469,13 +901,12 @@ int nn4mg_step(nn4mg_step_t S, double *C, double *u, double *v, double *w, doubl
         hipLaunchKernelGGL(surface2_kernel, bgrid, bblk, 0, s, g, qw, p.sigma_t, c3(S->nrm), c3(S->Cd),
                            f3(S->st));
     } else {
-        hipLaunchKernelGGL(props_kernel, grid, blk, 0, s, g, P, (const double *)C, S->rho, S->mu, f3(S->Cd),
-                           f3(S->nrm));
-        hipLaunchKernelGGL(surface_kernel, grid, blk, 0, s, g, p.sigma_t, c3(S->nrm), c3(S->Cd), f3(S->st));
+        STEP_TRY(step_props(g, P, C, S->rho, S->mu, f3(S->Cd), f3(S->nrm), s), "props");
+        STEP_TRY(step_surface(g, p.sigma_t, c3(S->nrm), c3(S->Cd), f3(S->st), s), "surface");
     }
 
     // Stage 1: hydrostatic + surface-tension pressure, warm-started from p_hs
-    hipLaunchKernelGGL(rhs_hydrostatic_kernel, grid, blk, 0, s, g, p.g, c3(S->st), (const double *)S->rho, S->b);
+    STEP_TRY(step_rhs_hydrostatic(g, p.g, c3(S->st), S->rho, S->b, s), "hydrostatic right-hand side");
     STEP_TRY(hipGetLastError(), "step kernels");
     STEP_TRY(hipMemcpyAsync(S->px, p_hs, g.n * sizeof(double), hipMemcpyDeviceToDevice, s), "hipMemcpyAsync");
     if ((rc = pressure_solve(S, 0, p.mg_cycles, info, &ms_mg))) return rc;
@@ -1498,22 +929,10 @@ int nn4mg_step(nn4mg_step_t S, double *C, double *u, double *v, double *w, doubl
             nxt = t;
             continue;
         }
-        hipLaunchKernelGGL(advection_kernel, bgrid, bblk, 0, s, g, c3(cur), f3(S->adv));
-        hipLaunchKernelGGL(pg_velocity_kernel, bgrid, bblk, 0, s, g, c3(cur), c3(S->adv), (const double *)S->rho,
-                           (const double *)S->mu, f3(S->kq));
-        {
-            MomIn in;
-            in.u[0] = p_hs;
-            in.u[1] = p_nh;
-            in.u[2] = S->rho;
-            for (int c = 0; c < 3; ++c) {
-                in.u[3 + c] = cur[c];
-                in.u[6 + c] = S->kq[c];
-                in.u[9 + c] = S->st[c];
-            }
-            hipLaunchKernelGGL(momentum_lds_kernel, mom_grid(g), dim3(MT_X * MT_Y), 0, s, g, P, c3(q), in,
-                               c3(S->adv), f3(S->qt), f3(nxt));
-        }
+        STEP_TRY(step_advection(g, c3(cur), f3(S->adv), s), "advection");
+        STEP_TRY(step_pg_velocity(g, c3(cur), c3(S->adv), S->rho, S->mu, f3(S->kq), s), "velocity diffusivity");
+        STEP_TRY(step_momentum(g, P, c3(q), p_hs, p_nh, S->rho, c3(cur), c3(S->kq), c3(S->st), c3(S->adv), f3(S->qt),
+                               f3(nxt), s), "momentum");
         double **t = cur;
         cur = nxt;
         nxt = t;
@@ -1523,13 +942,11 @@ int nn4mg_step(nn4mg_step_t S, double *C, double *u, double *v, double *w, doubl
     // Stage 3: non-hydrostatic corrections; the corrected velocity lands in q
     double **qin = S->qt;
     for (int it = 0; it < p.n_corr; ++it) {
-        hipLaunchKernelGGL(rhs_nonhydrostatic_kernel, grid, blk, 0, s, g, p.dt, c3(qin), (const double *)S->rho,
-                           S->b);
+        STEP_TRY(step_rhs_nonhydrostatic(g, p.dt, c3(qin), S->rho, S->b, s), "non-hydrostatic right-hand side");
         STEP_TRY(launch_fill(S->px, g.n, 0.0, s), "fill");
         if ((rc = pressure_solve(S, 1 + it, p.mg_cycles_nh > 0 ? p.mg_cycles_nh : p.mg_cycles, info, &ms_mg)))
             return rc;
-        hipLaunchKernelGGL(correct_kernel, grid, blk, 0, s, g, p.dt, (const double *)S->px, (const double *)S->rho,
-                           c3(qin), f3(q), p_nh);
+        STEP_TRY(step_correct(g, p.dt, S->px, S->rho, c3(qin), f3(q), p_nh, s), "correction");
         qin = q;
     }
     if (p.n_corr == 0) hipLaunchKernelGGL(copy3_kernel, grid, blk, 0, s, g.n, c3(S->qt), f3(q));
@@ -1540,10 +957,9 @@ int nn4mg_step(nn4mg_step_t S, double *C, double *u, double *v, double *w, doubl
         hipLaunchKernelGGL(pg_volume_fraction2_kernel, bgrid, bblk, 0, s, g, qw, p.dt, (const double *)C,
                            c3(S->Cd), c3(q), (const double *)S->tmp, f3(S->kq));
     else
-        hipLaunchKernelGGL(pg_volume_fraction_kernel, grid, blk, 0, s, g, p.dt, (const double *)C, c3(S->Cd), c3(q),
-                           (const double *)S->tmp, f3(S->kq));
-    hipLaunchKernelGGL(volume_fraction_kernel, grid, blk, 0, s, g, p.dt, (const double *)C, c3(S->kq), c3(q),
-                       c3(S->Cd), S->b);
+        STEP_TRY(step_pg_volume_fraction(g, p.dt, C, c3(S->Cd), c3(q), S->tmp, f3(S->kq), s),
+                 "volume-fraction diffusivity");
+    STEP_TRY(step_volume_fraction(g, p.dt, C, c3(S->kq), S->tmp, S->b, s), "volume fraction");
     STEP_TRY(hipMemcpyAsync(C, S->b, g.n * sizeof(double), hipMemcpyDeviceToDevice, s), "hipMemcpyAsync");
     STEP_TRY(hipGetLastError(), "step kernels");
     STEP_TRY(hipEventRecord(S->ev[1], s), "hipEventRecord");
