@@ -61,7 +61,8 @@ struct FTile {
     // first sweep: one vertical strip of R1 cells per thread, NST strips per column
     static constexpr int R1 = strip_rows(QX, QY);
     static constexpr int NST = (QY + R1 - 1) / R1;
-    static constexpr int NT1 = NST * QX;                            // threads with a strip
+    static constexpr int NT1 = NST * QX;                            // threads with a strip of their own
+    static constexpr bool EXACT = NST * R1 == QY;                   // no strip reaches past the region
     static constexpr int CX = TX / 2 + 4, CY = TY / 2 + 4, CN = CX * CY;  // coarse footprint
     static constexpr int NPREC = (CN + FT - 1) / FT;
 };
@@ -261,8 +262,18 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
     make_fgeo<TX, RY>(G, a, i0, j0);
     FPre<T, KT, TX, RY, ADD, XIN> pA, pB;
     Run<T> r1[TL::R1], r2[RY];
-    const bool act1 = (int)threadIdx.x < TL::NT1;
-    const int s1q = min((int)threadIdx.x, TL::NT1 - 1) / TL::QX;   // strip of this thread
+    // Strip of this thread.  The march exists in two shapes.  LEAN: threads
+    // beyond the strips repeat the last one (and write the same values to the
+    // same cells), which keeps the running sums off any divergent path (each
+    // merge point copies every one of them), and the steady steps work out no
+    // halo rule along z (scalar instructions were a third of the march's).  In
+    // FP64 that shape's registers are allocated worse and spill, except in
+    // 16-wide tiles without a coefficient, so those threads idle there.
+    // us at 256^3 and 256 x 256 x 512 (FP16-stored k), idle and lean: FP32 nodal 119
+    // and 113, constant 82 and 75, FP16 222 and 202; FP64 nodal 181 and 227.
+    constexpr bool LEAN = sizeof(T) == 4 || !(HK || TL::EXACT);
+    const bool act1 = LEAN || (int)threadIdx.x < TL::NT1;
+    const int s1q = min((int)threadIdx.x, TL::NT1 - 1) / TL::QX;
     const int s1x = min((int)threadIdx.x, TL::NT1 - 1) - s1q * TL::QX;
 
     const T *bp = (const T *)a.b;
@@ -279,18 +290,21 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
     // holding a load in flight is copied at the loop's back edge (a copy would
     // wait for every outstanding load and undo the two-plane prefetch).
     // (coarse values first: they are staged one step before the rest)
-    auto fetch_kc = [&](FPre<T, KT, TX, RY, ADD, XIN> &p, int zi) {
-        const int K = zi >> 1;
+    // in_z (lean steady steps): the plane and its coarse planes lie in the grid,
+    // no halo rule along z.
+    auto fetch_kc = [&](auto in_z, FPre<T, KT, TX, RY, ADD, XIN> &p, int zi) {
+        constexpr bool IN_Z = decltype(in_z)::value;
+        const int K = zi >> 1, K2 = K + ((zi & 1) ? 1 : -1);
         int s1 = 1, s2 = 1;
-        const size_t p1 = cplane * (size_t)fold(K, a.cnz, a.g.bc[4], a.g.bc[5], s1);
-        const size_t p2 = cplane * (size_t)fold(K + ((zi & 1) ? 1 : -1), a.cnz, a.g.bc[4], a.g.bc[5], s2);
+        const size_t p1 = cplane * (size_t)(IN_Z ? K : fold(K, a.cnz, a.g.bc[4], a.g.bc[5], s1));
+        const size_t p2 = cplane * (size_t)(IN_Z ? K2 : fold(K2, a.cnz, a.g.bc[4], a.g.bc[5], s2));
 #pragma unroll
         for (int q = 0; q < TL::NPREC; ++q) {
             p.c1[q] = ep[p1 + (size_t)G.coff[q]];
             p.c2[q] = ep[p2 + (size_t)G.coff[q]];
         }
         int sk_ = 1;
-        const size_t pz = plane * (size_t)fold(zi, nz, a.g.bc[4], a.g.bc[5], sk_);
+        const size_t pz = plane * (size_t)(IN_Z ? zi : fold(zi, nz, a.g.bc[4], a.g.bc[5], sk_));
         if constexpr (HK) {
 #pragma unroll
             for (int q = 0; q < TL::NPRE; ++q) p.k[q] = kp[pz + (size_t)G.off[q]];
@@ -309,7 +323,7 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
         if (MODE != 0 || (zi - 1 >= z0 - 1 && zi - 1 <= z1)) {
             const int zb = MODE == 2 ? min(max(zi - 1, z0 - 1), z1) : zi - 1;
             int sb = 1;
-            const size_t pb = plane * (size_t)fold(zb, nz, a.g.bc[4], a.g.bc[5], sb);
+            const size_t pb = plane * (size_t)(MODE == 1 && LEAN ? zb : fold(zb, nz, a.g.bc[4], a.g.bc[5], sb));
 #pragma unroll
             for (int q = 0; q < TL::R1; ++q) p.b1[q] = bp[pb + (size_t)G.boff[q]];
         }
@@ -323,18 +337,20 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
         }
     };
     auto fetch = [&](FPre<T, KT, TX, RY, ADD, XIN> &p, int zi) {
-        fetch_kc(p, zi);
+        fetch_kc(std::false_type{}, p, zi);
         fetch_b(std::integral_constant<int, 0>{}, p, zi);
     };
 
     // The coarse footprint of plane zi, interpolated in z, into sc[zi & 1].
     // Staged one step ahead (before the barrier that precedes the second
     // sweep), so the commit needs no barrier of its own before reading it.
-    auto stage_c = [&](const FPre<T, KT, TX, RY, ADD, XIN> &p, int zi) {
+    auto stage_c = [&](auto in_z, const FPre<T, KT, TX, RY, ADD, XIN> &p, int zi) {
         const int K = zi >> 1;
         int s1 = 1, s2 = 1;
-        (void)fold(K, a.cnz, a.g.bc[4], a.g.bc[5], s1);
-        (void)fold(K + ((zi & 1) ? 1 : -1), a.cnz, a.g.bc[4], a.g.bc[5], s2);
+        if constexpr (!decltype(in_z)::value) {
+            (void)fold(K, a.cnz, a.g.bc[4], a.g.bc[5], s1);
+            (void)fold(K + ((zi & 1) ? 1 : -1), a.cnz, a.g.bc[4], a.g.bc[5], s2);
+        }
 #pragma unroll
         for (int q = 0; q < TL::NPREC; ++q)
             if (q * FT + (int)threadIdx.x < TL::CN) {
@@ -345,9 +361,9 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
 
     // P e (plus x, XIN) of plane zi into sx[buf] from its staged coarse
     // footprint, the coefficient into sk[buf].
-    auto commit = [&](const FPre<T, KT, TX, RY, ADD, XIN> &p, int zi, int buf) {
+    auto commit = [&](auto in_z, const FPre<T, KT, TX, RY, ADD, XIN> &p, int zi, int buf) {
         int sz = 1;
-        if constexpr (XIN) (void)fold(zi, nz, a.g.bc[4], a.g.bc[5], sz);
+        if constexpr (XIN && !decltype(in_z)::value) (void)fold(zi, nz, a.g.bc[4], a.g.bc[5], sz);
         const T *scp = sc[zi & 1];
 #pragma unroll
         for (int q = 0; q < TL::NPRE; ++q) {
@@ -380,14 +396,15 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
         constexpr int MODE = decltype(mode_tag)::value;
         constexpr bool ST = MODE == 1;  // steady: every condition below holds
         constexpr bool FX = MODE != 0;  // fixed loads
-        commit(p, zi, buf);
+        const std::integral_constant<bool, ST && LEAN> in_z{};
+        commit(in_z, p, zi, buf);
         bool bzneg = false;
-        {
+        if constexpr (!(ST && LEAN)) {
             int sb = 1;
             (void)fold(zi - 1, nz, a.g.bc[4], a.g.bc[5], sb);
             bzneg = sb < 0;
         }
-        if (FX || zi + 2 <= z1 + 1) fetch_kc(p, zi + 2);
+        if (FX || zi + 2 <= z1 + 1) fetch_kc(in_z, p, zi + 2);
 
         // first sweep: absorb plane zi down the thread's strip, completing y1(zi - 1)
         const int yb = (zi - 1) & 1;
@@ -395,7 +412,7 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
             // window rows j = 0 .. R1 + 1 of the input plane (region rows
             // s1q R1 - 1 .. s1q R1 + R1), clamped into the staged plane
             auto wrow = [&](int j) {
-                const int py = min(s1q * TL::R1 + j, TL::PY - 1);
+                const int py = (TL::EXACT && LEAN) ? s1q * TL::R1 + j : min(s1q * TL::R1 + j, TL::PY - 1);
                 const int c = py * TL::PX + (s1x + 1);
                 return row_at<T, HK>(sx[buf], c, sk[buf], c);
             };
@@ -407,8 +424,9 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
                 const int qy = s1q * TL::R1 + q;
                 const T bv = XIN ? p.b1[q] - bm : p.b1[q];
                 const T bq = (G.bneg[q] != bzneg) ? -bv : bv;
-                if (qy < TL::QY) sb[yb][qy * TL::QX + s1x] = bq;
-                if ((ST || zi >= z0) && qy < TL::QY)
+                const bool in = (TL::EXACT && LEAN) || qy < TL::QY;
+                if (in) sb[yb][qy * TL::QX + s1x] = bq;
+                if ((ST || zi >= z0) && in)
                     sy[yb][qy * TL::QX + s1x] = jacobi<T, HK>(r1[q], ps, bq, cw, om_w0, om, icv);
                 absorb<T, HK>(r1[q], ps, zi == z0 - 2);
                 w0 = w1;
@@ -416,12 +434,12 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
             }
         }
         // the next plane's coarse footprint (its commit reads it after the barrier below)
-        if (FX || zi + 1 <= z1 + 1) stage_c(pn, zi + 1);
+        if (FX || zi + 1 <= z1 + 1) stage_c(in_z, pn, zi + 1);
         __syncthreads();
         if (ST || zi >= z0) {
             // second sweep: absorb y1(zi - 1) with the coefficient plane zi - 1,
             // completing the output plane zi - 2
-            const int kb = (buf + 2) % 3;
+            const int kb = (buf == 0 ? 2 : buf - 1);
             // window rows j = 0 .. RY + 1 of the first-sweep plane (rows RY ly + j),
             // coefficient one row and column further in the input region
             auto wrow = [&](int j) {
@@ -452,12 +470,12 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
         }
         // right-hand sides of plane zi + 2's step, into the registers just consumed
         if (FX || zi + 2 <= z1 + 1) fetch_b(mode_tag, p, zi + 2);
-        buf = (buf + 1) % 3;
+        buf = buf == 2 ? 0 : buf + 1;
     };
 
     fetch(pA, z0 - 2);
     fetch(pB, z0 - 1);
-    stage_c(pA, z0 - 2);
+    stage_c(std::false_type{}, pA, z0 - 2);
     __syncthreads();
     const std::integral_constant<int, 0> gen{};
     const std::integral_constant<int, 1> steady{};
@@ -475,7 +493,9 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(2))) void sw
             step(first, pA, pB, zi);
             step(first, pB, pA, zi + 1);
         }
-        for (; zi + 3 <= z1 + 1; zi += 2) {
+        // lean: the coarse planes of plane zi + 3 lie in the grid up to zi + 3 = nz - 2
+        const int zs = LEAN ? min(z1 - 2, nz - 5) : z1 - 2;
+        for (; zi <= zs; zi += 2) {
             step(steady, pA, pB, zi);
             step(steady, pB, pA, zi + 1);
         }
