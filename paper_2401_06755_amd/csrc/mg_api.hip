@@ -123,6 +123,21 @@ TileShape default_tiles_for(int nx, int ny, int nz, int kclass, bool fused, int 
     return default_tiles(nx, ny, nz, zmul);
 }
 
+// Residual shape of flexible CG around an FP32 cycle: 64-wide tiles from 64
+// cells on and a power-of-two chunk of at most 64 planes that keeps 512
+// workgroups.  The pass also sums p . A p, in the order of its workgroups, and
+// FP32 rounding of the next residual carries that sum's last bit into the
+// fourth digit of what the solve reports; march_tiles' shape would gain 7 us of
+// 285 an iteration at 192 x 160 x 224 (nothing at 256^3) for other digits.
+TileShape fcg_resid_tiles(int nx, int ny, int nz)
+{
+    if (nx < 64) return default_tiles(nx, ny, nz);
+    const long tiles = (long)((nx + 63) / 64) * ((ny + 7) / 8);
+    int zc = 64;
+    while (zc > 2 && tiles * ((nz + zc - 1) / zc) < 512) zc /= 2;
+    return make_tiles(nx, ny, nz, zc, 64, 2);
+}
+
 int count_levels(int nx, int ny, int nz, int min_coarse)
 {
     int L = 1;
@@ -300,12 +315,18 @@ constexpr size_t kTailLdsBudget = 128 * 1024;
 // its launch; up to about a thousand cells the single workgroup wins.
 constexpr size_t kTailMaxCells = 1024;
 
-// First level of the coarse end (0: none), and whether its one-workgroup kernel
-// fits in FP64, which the matrix of the dense form (dense_kernel) is built with.
+bool fcg_f32(const nn4mg_config *c) { return c->outer == NN4MG_OUTER_FCG && c->precision != NN4MG_PREC_FP64; }
+
+// First level of the coarse end (0: none), and whether it takes the dense form
+// (dense_kernel).  Its one-workgroup kernel has to fit in FP64, which builds the
+// matrix.  Flexible CG around an FP32 cycle keeps the one-workgroup kernel: the
+// fifth digit of its residual follows the rounding of every FP32 level, so the
+// FP64 matrix would change what it reports, for 9 us of 530 an iteration at
+// 256^3.
 struct TailChoice {
     int first = 0;
     size_t cells = 0;  // of the first level
-    bool fits_f64 = false;
+    bool dense = false;
 };
 
 TailChoice choose_tail(const nn4mg_config *c)
@@ -341,7 +362,7 @@ TailChoice choose_tail(const nn4mg_config *c)
     }
     if (out.first > 0) {
         out.cells = cells_of(out.first);
-        out.fits_f64 = field_cells(out.first) * 8 + 48 * 1024 <= kTailLdsBudget;
+        out.dense = !fcg_f32(c) && field_cells(out.first) * 8 + 48 * 1024 <= kTailLdsBudget;
     }
     return out;
 }
@@ -375,7 +396,7 @@ size_t bytes_for(const nn4mg_config *c, bool dense)
     b += 8 * nc * nc + sizeof(SolveState) + 8 * maxblk + 64 + 4 * kCoefFlags;
     b += kArenaAlign * (size_t)(5 * L + 12);  // alignment of each field in the arena
     const TailChoice tail = choose_tail(c);
-    if (dense && tail.fits_f64) b += 8 * tail.cells * tail.cells;
+    if (dense && tail.dense) b += 8 * tail.cells * tail.cells;
     if (c->outer == NN4MG_OUTER_FCG) b += 4 * 8 * (size_t)c->nx * c->ny * c->nz + 8 * (size_t)fcg_partials_needed();
     return b;
 }
@@ -1010,6 +1031,7 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         const int zmul = group ? kGroupTileCopies : 1;
         for (int c = 0; c < 3; ++c)
             V.tiles[c] = default_tiles_for(V.nx, V.ny, V.nz, c, cfg->nu_post == 2 && H->L >= 2, zmul);
+        if (l == 0 && fcg_f32(cfg)) V.tiles[NN4MG_KCLASS_FINE_RESID] = fcg_resid_tiles(V.nx, V.ny, V.nz);
         if (V.tiles[0].blocks() > maxblk) maxblk = V.tiles[0].blocks();
         if (nodal) TRY(dalloc(H, &V.k, V.n));
         const bool single = (H->L == 1);
@@ -1036,7 +1058,7 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
     H->nc = (int)C.n;
     const TailChoice tail = choose_tail(cfg);
     H->tail = tail.first;
-    H->use_dense = dense && tail.fits_f64;
+    H->use_dense = dense && tail.dense;
     H->fused = cfg->nu_post == 2 && H->L >= 2;
     if (group && (H->L < 2 || H->tail == 0 || !H->fused || cfg->outer != NN4MG_OUTER_STATIONARY)) {
         nn4mg_destroy(H);

@@ -52,10 +52,9 @@ __device__ __forceinline__ T corner_prod(const T *v, int o, const T *k, int ok)
 template <typename T, int W, int WK>
 __device__ __forceinline__ T other_prod(const T *v, int o, const T *k, int ok)
 {
-#pragma clang fp contract(off)
-    const T ma = k[ok - WK] * v[o - W], mc = k[ok + WK] * v[o + W];
     return neighbour_plane(corner_prod<T, W, WK>(v, o, k, ok),
-                           cross_sum(ma, mc, pair_prod(k[ok - 1], v[o - 1], k[ok + 1], v[o + 1])));
+                           cross_prod(k[ok - WK], v[o - W], k[ok + WK], v[o + W],
+                                      pair_prod(k[ok - 1], v[o - 1], k[ok + 1], v[o + 1])));
 }
 
 // One Jacobi update of the cell at c of field v (row stride W, plane stride WP);

@@ -149,7 +149,7 @@ struct Run {
 // its centre, for the field v, the coefficient k and the product k v.
 template <typename T>
 struct Row {
-    T h, m, kh, km, ph, pm;
+    T h, m, kh, km, ph;
 };
 
 template <typename T, bool HK>
@@ -165,7 +165,6 @@ __device__ __forceinline__ Row<T> row_at(const T *v, int c, const T *k, int ck)
         o.kh = kl + kr;
         o.km = km;
         o.ph = pair_prod(kl, vl, kr, vr);
-        o.pm = km * vm;
     }
     return o;
 }
@@ -185,7 +184,7 @@ __device__ __forceinline__ PS<T> col_sums(const Row<T> &a, const Row<T> &b, cons
         o.ka = Dk + Dk;
         o.ko = neighbour_plane(Dk, cross_sum(a.km, c.km, b.kh));
         o.pa = Dp + Dp;
-        o.po = neighbour_plane(Dp, cross_sum(a.pm, c.pm, b.ph));
+        o.po = neighbour_plane(Dp, cross_prod(a.km, a.m, c.km, c.m, b.ph));
     }
     return o;
 }
