@@ -1248,8 +1248,9 @@ int read_header(nn4mg_hier *H, StateHeader *hd)
     return NN4MG_OK;
 }
 
-// ||b - mean|| (mean only for singular problems) into st->nb, st->bmean.
-int enqueue_b_norm(nn4mg_hier *H, const double *b)
+// The state of a new solve, with ||b - mean|| (mean only for singular problems)
+// in st->nb, st->bmean.
+int enqueue_state(nn4mg_hier *H, const double *b, double rtol, int max_cycles, int fixed)
 {
     const size_t n = H->lv[0].n;
     hipStream_t s = H->stream;
@@ -1258,8 +1259,7 @@ int enqueue_b_norm(nn4mg_hier *H, const double *b)
         HIP_TRY(launch_reduce(H->partials, sum_blocks(n), 1.0 / (double)n, &H->st->bmean, s));
     }
     HIP_TRY(launch_sum_partials(b, n, H->singular ? &H->st->bmean : nullptr, 2, H->partials, s));
-    HIP_TRY(launch_reduce(H->partials, sum_blocks(n), 1.0, H->scal, s));
-    HIP_TRY(launch_set_nb(H->st, H->scal, s));
+    HIP_TRY(launch_begin(H->st, H->partials, sum_blocks(n), rtol, max_cycles, fixed, H->singular, s));
     return NN4MG_OK;
 }
 
@@ -1456,13 +1456,16 @@ int solve_begin(nn4mg_hier *H, const double *b, double *x, double rtol, int max_
     H->solve_enqueued = 0;
     H->solve_prev_last = -1.0;
     H->solve_planned = fixed ? max_cycles : (max_cycles < 4 ? max_cycles : 4);
-    HIP_TRY(launch_init_state(H->st, rtol, max_cycles, fixed, s));
     H->cur_tag = 0;
     H->prof_solve_begin = H->prof_cls.size();
-    if ((rc = enqueue_b_norm(H, b))) return rc;
+    if ((rc = enqueue_state(H, b, rtol, max_cycles, fixed))) return rc;
     if (H->cfg.outer == NN4MG_OUTER_FCG) return enqueue_fcg_start(H, b, x);
     if ((rc = enqueue_resid_for_cycle(H, b, x, H->singular ? &H->st->bmean : nullptr, true, &H->st->done))) return rc;
-    HIP_TRY(launch_finish_norm(H->st, H->partials, resid_blocks(H), s, stop_in_chain(H) ? 1 : 0));
+    // The first residual is judged in the first cycle's chain, as every later one
+    // is.  Not for a copy of a batched group, whose cycles are the group's, nor
+    // where no cycle follows.
+    if (!stop_in_chain(H) || H->view_of || H->solve_planned < 1)
+        HIP_TRY(launch_finish_norm(H->st, H->partials, resid_blocks(H), s, stop_in_chain(H) ? 1 : 0));
     return NN4MG_OK;
 }
 
@@ -1660,7 +1663,7 @@ int batch_enqueue_cycles(nn4mg_hier *G, int n, int k)
 int hier_mark_idle(nn4mg_hier *H)
 {
     static const int one = 1;
-    HIP_TRY(launch_init_state(H->st, 0.0, 0, 1, H->stream));
+    HIP_TRY(launch_begin(H->st, nullptr, 0, 0.0, 0, 1, 0, H->stream));
     HIP_TRY(hipMemcpyAsync(&H->st->done, &one, sizeof(int), hipMemcpyHostToDevice, H->stream));
     HIP_TRY(hipStreamSynchronize(H->stream));
     return NN4MG_OK;

@@ -180,9 +180,10 @@ hipError_t launch_sum_partials(const double *v, size_t n, const double *shift, i
                                hipStream_t s);
 // out[0] = scale * sum(partials[0..n))  (single workgroup, fixed tree)
 hipError_t launch_reduce(const double *partials, int n, double scale, double *out, hipStream_t s);
-// Reset the solve state; set_nb: nb = sqrt(*sumsq), and done at once if nb == 0.
-hipError_t launch_init_state(SolveState *st, double rtol, int max_cycles, int fixed, hipStream_t s);
-hipError_t launch_set_nb(SolveState *st, const double *sumsq, hipStream_t s);
+// Reset the solve state, with nb the root of the summed partials (and done at once
+// if it is zero or not finite) unless n is 0.
+hipError_t launch_begin(SolveState *st, const double *partials, int n, double rtol, int max_cycles, int fixed,
+                        int keep_mean, hipStream_t s);
 // Stopping rule after a residual: consumes partials of r^2.
 // Stopping rule on the residual partials; mark_taken = 1 tells the stopping
 // workgroup of the next restriction chain that this residual is done.
