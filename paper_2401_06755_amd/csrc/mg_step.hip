@@ -188,83 +188,111 @@ struct QLds {
     double p[3][QPN]; // y pass: M on r[0], the derivative (or K) filter on r[1], M on r[1]
 };
 
-// Index up to two cells outside folded as fold2; indices further out (the
-// halo of a ragged block's cells beyond the grid, which feed no output) are
-// clamped into range.
-__device__ inline int qfold(int i, int n, unsigned odd, unsigned lo_bit, unsigned hi_bit, double &s)
+// Index up to two cells outside folded onto the cell it mirrors; indices further
+// out (the halo of a ragged block's cells beyond the grid, which feed no output)
+// are clamped into range.
+__device__ inline int qfold(int i, int n)
 {
-    const int f = fold2(i, n, odd, lo_bit, hi_bit, s);
+    const int f = i < 0 ? -1 - i : (i >= n ? 2 * n - 1 - i : i);
     return min(max(f, 0), n - 1);
 }
 
-// A field at unfolded (i, j, k) with the two-cell halo of rule odd.
-// Each staging functor splits into fetch (the global loads and the sign or
-// halo case of an unfolded (i, j, k)) and value (the staged value from the
-// fetched raw data), so the loads of the next field can be in flight while
-// the current field's passes run.
+// The cells of the staged region that this thread stages: where each is read
+// from (32 bits: the state of a grid of 2^32 cells is beyond the memory) and
+// which faces its halo crosses (bits as in the boundary rules; for a cell
+// below the bottom its mirror distance m in the bits from 8 on).  Worked out
+// once per kernel: for every field anew it was most of the integer work.
+struct QGeo {
+    static constexpr int NR = (QSN + QT - 1) / QT;
+    unsigned off[NR], face[NR];
+};
+__device__ inline QGeo qgeo(const Grid &g, int i0, int j0, int k0)
+{
+    QGeo o;
+#pragma unroll
+    for (int q = 0; q < QGeo::NR; ++q) {
+        const int idx = min((int)threadIdx.x + q * QT, QSN - 1);
+        const int i = i0 + idx % QS - 2, j = j0 + (idx / QS) % QS - 2, k = k0 + idx / (QS * QS) - 2;
+        o.off[q] = (unsigned)at(g, qfold(i, g.nx), qfold(j, g.ny), qfold(k, g.nz));
+        o.face[q] = (i < 0 ? 1u : 0u) | (i >= g.nx ? 2u : 0u) | (j < 0 ? 4u : 0u) | (j >= g.ny ? 8u : 0u) |
+                    (k >= g.nz ? 32u : 0u) | (k < 0 ? 16u | (unsigned)(-1 - k) << 8 : 0u);
+    }
+    return o;
+}
+
+// Each staging functor splits into fetch (the global loads of a cell) and value
+// (the staged value from the fetched raw data and the faces crossed), so the
+// loads of the next field can be in flight while the current field's passes run.
+
+// A field with the two-cell halo of rule odd.
 struct QTap {
     const double *u;
     unsigned odd;
-    Grid g;
-    struct Raw {
-        double v;
-        bool neg;
-    };
-    __device__ Raw fetch(int i, int j, int k) const
-    {
-        double s = 1.0;
-        const int fi = qfold(i, g.nx, odd, 1u, 2u, s);
-        const int fj = qfold(j, g.ny, odd, 4u, 8u, s);
-        const int fk = qfold(k, g.nz, odd, 16u, 32u, s);
-        return {u[at(g, fi, fj, fk)], s < 0.0};
-    }
-    __device__ double value(const Raw &r) const { return r.neg ? -r.v : r.v; }
-    __device__ double operator()(int i, int j, int k) const { return value(fetch(i, j, k)); }
+    typedef double Raw;
+    __device__ Raw fetch(unsigned off, unsigned) const { return u[off]; }
+    __device__ double value(Raw r, unsigned face) const { return (__popc(face & odd) & 1) ? -r : r; }
 };
 
-// p_hs at unfolded (i, j, k): +mirror on the sides, -mirror on top, and below
-// the bottom the mirror plus (2m + 1) g h rho of the mirrored cell (rho +mirror
-// on the sides).
+// p_hs: +mirror on the sides, -mirror on top, and below the bottom the mirror
+// plus (2m + 1) g h rho of the mirrored cell (rho +mirror on the sides).
 struct QPhs {
     const double *p, *rho;
-    Grid g;
     double gh;
     struct Raw {
         double p, r;
-        int m;  // below the bottom: the mirror distance m (>= 0); -1 inside; -2 above the top
     };
-    __device__ Raw fetch(int i, int j, int k) const
+    __device__ Raw fetch(unsigned off, unsigned face) const { return {p[off], (face & 16u) ? rho[off] : 0.0}; }
+    __device__ double value(const Raw &o, unsigned face) const
     {
-        double s = 1.0;
-        const int fi = qfold(i, g.nx, 0u, 1u, 2u, s);
-        const int fj = qfold(j, g.ny, 0u, 4u, 8u, s);
-        const int fk = qfold(k, g.nz, 0u, 16u, 32u, s);
-        const size_t idx = at(g, fi, fj, fk);
-        Raw o;
-        o.p = p[idx];
-        o.r = k < 0 ? rho[idx] : 0.0;
-        o.m = k < 0 ? -1 - k : (k >= g.nz ? -2 : -1);
-        return o;
+        if (face & 16u) return o.p + (double)(2 * (face >> 8) + 1) * gh * o.r;
+        return (face & 32u) ? -o.p : o.p;
     }
-    __device__ double value(const Raw &o) const
-    {
-        if (o.m >= 0) return o.p + (double)(2 * o.m + 1) * gh * o.r;
-        return o.m == -2 ? -o.p : o.p;
-    }
-    __device__ double operator()(int i, int j, int k) const { return value(fetch(i, j, k)); }
 };
 
 template <typename A, typename B>
-struct QMul {
+struct QPair {
     A a;
     B b;
     struct Raw {
         typename A::Raw a;
         typename B::Raw b;
     };
-    __device__ Raw fetch(int i, int j, int k) const { return {a.fetch(i, j, k), b.fetch(i, j, k)}; }
-    __device__ double value(const Raw &r) const { return a.value(r.a) * b.value(r.b); }
-    __device__ double operator()(int i, int j, int k) const { return value(fetch(i, j, k)); }
+    __device__ Raw fetch(unsigned off, unsigned face) const { return {a.fetch(off, face), b.fetch(off, face)}; }
+};
+template <typename A, typename B>
+struct QMul : QPair<A, B> {
+    __device__ double value(const typename QPair<A, B>::Raw &r, unsigned face) const
+    {
+        return this->a.value(r.a, face) * this->b.value(r.b, face);
+    }
+};
+// Sum of two fields, each with its own boundary rule.
+template <typename A, typename B>
+struct QSum : QPair<A, B> {
+    __device__ double value(const typename QPair<A, B>::Raw &r, unsigned face) const
+    {
+        return this->a.value(r.a, face) + this->b.value(r.b, face);
+    }
+};
+
+// A component of the surface tension plus w rho (rho +mirror at every face);
+// rho is read only where w is not zero.
+struct QForce {
+    QTap st;
+    const double *rho;
+    double w;
+    struct Raw {
+        double st, r;
+    };
+    __device__ Raw fetch(unsigned off, unsigned face) const
+    {
+        return {st.fetch(off, face), w != 0.0 ? rho[off] : 0.0};
+    }
+    __device__ double value(const Raw &o, unsigned face) const
+    {
+        const double v = st.value(o.st, face);
+        return w != 0.0 ? v + w * o.r : v;
+    }
 };
 
 // The next field's staging in registers: fetch issues its loads, commit
@@ -272,42 +300,29 @@ struct QMul {
 // pass, the only reader of the staged field, is then done on every thread).
 template <typename V>
 struct QNext {
-    static constexpr int NR = (QSN + QT - 1) / QT;
-    typename V::Raw r[NR];
-    __device__ void fetch(const V &v, int i0, int j0, int k0)
+    typename V::Raw r[QGeo::NR];
+    __device__ void fetch(const V &v, const QGeo &G)
     {
-        const int t = threadIdx.x;
 #pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const int idx = min(t + q * QT, QSN - 1);
-            const int x = idx % QS, y = (idx / QS) % QS, z = idx / (QS * QS);
-            r[q] = v.fetch(i0 + x - 2, j0 + y - 2, k0 + z - 2);
-        }
+        for (int q = 0; q < QGeo::NR; ++q) r[q] = v.fetch(G.off[q], G.face[q]);
     }
-    __device__ void commit(QLds &L, const V &v) const
+    __device__ void commit(QLds &L, const V &v, const QGeo &G) const
     {
-        const int t = threadIdx.x;
 #pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const int idx = t + q * QT;
-            if (idx < QSN) L.s[idx] = v.value(r[q]);
+        for (int q = 0; q < QGeo::NR; ++q) {
+            const int idx = (int)threadIdx.x + q * QT;
+            if (idx < QSN) L.s[idx] = v.value(r[q], G.face[q]);
         }
     }
 };
 
-// Stage field v on the block at (i0, j0, k0) plus its two-cell halo.
+// Stage field v on the block plus its two-cell halo.
 template <typename V>
-__device__ inline void qstage(QLds &L, const V &v, int i0, int j0, int k0)
+__device__ inline void qstage(QLds &L, const V &v, const QGeo &G)
 {
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int r = 0; r < (QSN + QT - 1) / QT; ++r) {
-        const int idx = t + r * QT;
-        if (idx < QSN) {
-            const int x = idx % QS, y = (idx / QS) % QS, z = idx / (QS * QS);
-            L.s[idx] = v(i0 + x - 2, j0 + y - 2, k0 + z - 2);
-        }
-    }
+    QNext<V> n;
+    n.fetch(v, G);
+    n.commit(L, v, G);
 }
 
 // The x and y passes of the staged field: wa is G (derivatives) or K
@@ -408,9 +423,10 @@ __global__ __launch_bounds__(QT) void props2_kernel(Grid g, Phys P, const QW F, 
 {
     __shared__ QLds L;
     const BCell X = bcell(g);
+    const QGeo cells = qgeo(g, X.i0, X.j0, X.k0);
     const size_t id = X.id;
     double d[4];
-    qstage(L, QTap{C, kEven, g}, X.i0, X.j0, X.k0);
+    qstage(L, QTap{C, kEven}, cells);
     qderiv<true>(L, F, d);
     if (!X.valid) return;
     const double c0 = C[id];
@@ -431,10 +447,11 @@ __global__ __launch_bounds__(QT) void surface2_kernel(Grid g, const QW F, double
 {
     __shared__ QLds L;
     const BCell X = bcell(g);
+    const QGeo cells = qgeo(g, X.i0, X.j0, X.k0);
     double kap = 0.0;
     for (int e = 0; e < 3; ++e) {
         double d[4];
-        qstage(L, QTap{nrm.p[e], rule_grad(e), g}, X.i0, X.j0, X.k0);
+        qstage(L, QTap{nrm.p[e], rule_grad(e)}, cells);
         qderiv<true>(L, F, d);
         kap += d[e];
     }
@@ -448,11 +465,12 @@ __global__ __launch_bounds__(QT) void advection2_kernel(Grid g, const QW F, C3 q
 {
     __shared__ QLds L;
     const BCell X = bcell(g);
+    const QGeo cells = qgeo(g, X.i0, X.j0, X.k0);
     const size_t id = X.id;
     const double q0[3] = {q.p[0][id], q.p[1][id], q.p[2][id]};
     for (int c = 0; c < 3; ++c) {
         double d[4];
-        qstage(L, QTap{q.p[c], rule_vel(c), g}, X.i0, X.j0, X.k0);
+        qstage(L, QTap{q.p[c], rule_vel(c)}, cells);
         qderiv<true>(L, F, d);
         if (X.valid) adv.p[c][id] = q0[0] * (d[0] / F.ml) + q0[1] * (d[1] / F.ml) + q0[2] * (d[2] / F.ml);
     }
@@ -465,15 +483,16 @@ __global__ __launch_bounds__(QT) void pg_velocity2_kernel(Grid g, const QW F, C3
 {
     __shared__ QLds L;
     const BCell X = bcell(g);
+    const QGeo cells = qgeo(g, X.i0, X.j0, X.k0);
     const size_t id = X.id;
     const double eps_k = 1e-7, a_kabs = 1.0 / 16.0, a_ksq = 4.0, h = g.h;
     const double u = q.p[0][id], v = q.p[1][id], w = q.p[2][id];
     for (int c = 0; c < 3; ++c) {
         double d[4], am[4];
-        qstage(L, QTap{q.p[c], rule_vel(c), g}, X.i0, X.j0, X.k0);
+        qstage(L, QTap{q.p[c], rule_vel(c)}, cells);
         qderiv<true>(L, F, d);
         const double px = d[0] / F.ml, py = d[1] / F.ml, pz = d[2] / F.ml;
-        qstage(L, QTap{adv.p[c], kEven, g}, X.i0, X.j0, X.k0);
+        qstage(L, QTap{adv.p[c], kEven}, cells);
         qderiv<false>(L, F, am);
         const double a = 2.0 * (am[3] / F.ml - adv.p[c][id]);
         const double G = fabs(px) + fabs(py) + fabs(pz);
@@ -489,85 +508,76 @@ __global__ __launch_bounds__(QT) void pg_velocity2_kernel(Grid g, const QW F, C3
 
 // One predictor iteration with the quadratic filters: s_c = rho m_l adv_c +
 // f_lap(q_c, k_c) + f(p_hs + p_nh; w_c) + f(s_t,c; w_m) [- f(-g rho; w_m) for
-// c = z], the same residual as momentum_lds_kernel; 15 filters per cell.
+// c = z], the same residual as the linear march.  The filters are linear, so the
+// two pressures are summed while they are staged, and so are the surface tension
+// and the weight: 13 filtered fields.  Bound by its LDS passes at one workgroup
+// of 8 waves per compute unit (184 registers; held to 128 for a second workgroup
+// it spills 42, and the step takes 2.75 ms).  With 15 fields and the halo worked
+// out for each, 190 us at 80 x 64 x 160; now 152 us (the step 2.75 and 2.65 ms).
 __global__ __launch_bounds__(QT) void momentum2_kernel(Grid g, Phys P, const QW F, C3 qn, const double *p_hs,
                                                        const double *p_nh, const double *rho, C3 qh, C3 kq, C3 st,
                                                        C3 adv, F3 qt, F3 qnext)
 {
     __shared__ QLds L;
     const BCell X = bcell(g);
+    const QGeo cells = qgeo(g, X.i0, X.j0, X.k0);
     const size_t id = X.id;
-    const int i0 = X.i0, j0 = X.j0, k0 = X.k0;
     const double r0 = rho[id];
-    double ghs[4], gnh[4], rm[4];
+    double gp[4];
     // each field's loads are issued before the previous field's passes
-    const QPhs fphs{p_hs, rho, g, P.g * g.h};
-    const QTap fnh{p_nh, kOddTop, g}, frho{rho, kEven, g};
-    {
-        QNext<QPhs> n0;
-        n0.fetch(fphs, i0, j0, k0);
-        n0.commit(L, fphs);
-    }
-    {
-        QNext<QTap> n1;
-        n1.fetch(fnh, i0, j0, k0);
-        qderiv<true>(L, F, ghs);
-        n1.commit(L, fnh);
-    }
-    {
-        QNext<QTap> n2;
-        n2.fetch(frho, i0, j0, k0);
-        qderiv<true>(L, F, gnh);
-        n2.commit(L, frho);
-    }
+    using TP = QSum<QPhs, QTap>;
     using TM = QMul<QTap, QTap>;
     {
-        const TM m0{QTap{kq.p[0], kEven, g}, QTap{qh.p[0], rule_vel(0), g}};
-        QNext<TM> n3;
-        n3.fetch(m0, i0, j0, k0);
-        qderiv<false>(L, F, rm);
-        n3.commit(L, m0);
+        const TP fp{{QPhs{p_hs, rho, P.g * g.h}, QTap{p_nh, kOddTop}}};
+        QNext<TP> n0;
+        n0.fetch(fp, cells);
+        n0.commit(L, fp, cells);
     }
-    const double buoy = -P.g * rm[3];  // f(-g rho; w_m)
+    {
+        const TM m0{{QTap{kq.p[0], kEven}, QTap{qh.p[0], rule_vel(0)}}};
+        QNext<TM> n1;
+        n1.fetch(m0, cells);
+        qderiv<true>(L, F, gp);
+        n1.commit(L, m0, cells);
+    }
 #pragma unroll 1
     for (int c = 0; c < 3; ++c) {
-        const QTap tq{qh.p[c], rule_vel(c), g}, tk{kq.p[c], kEven, g}, ts{st.p[c], rule_grad(c), g};
+        const QTap tq{qh.p[c], rule_vel(c)}, tk{kq.p[c], kEven};
+        const QForce ts{QTap{st.p[c], rule_grad(c)}, rho, c == 2 ? P.g : 0.0};
         const double q0 = qh.p[c][id], kc = kq.p[c][id];
         // Eq. k-T: 1/2 [f(k q; w) + k f(q; w) - q f(k; w)]; f(k q) is staged
         double lkq, lq, lk;
         {
             QNext<QTap> n;
-            n.fetch(tq, i0, j0, k0);
+            n.fetch(tq, cells);
             lkq = qlap(L, F);
-            n.commit(L, tq);
+            n.commit(L, tq, cells);
         }
         {
             QNext<QTap> n;
-            n.fetch(tk, i0, j0, k0);
+            n.fetch(tk, cells);
             lq = qlap(L, F);
-            n.commit(L, tk);
+            n.commit(L, tk, cells);
         }
         {
-            QNext<QTap> n;
-            n.fetch(ts, i0, j0, k0);
+            QNext<QForce> n;
+            n.fetch(ts, cells);
             lk = qlap(L, F);
-            n.commit(L, ts);
+            n.commit(L, ts, cells);
         }
         double s = 0.5 * (lkq + kc * lq - q0 * lk);
-        s += ghs[c];
-        s += gnh[c];
+        s += gp[c];
         double t4[4];
         {
             // the next component's product field
             const int cn = c < 2 ? c + 1 : c;
-            const TM mn{QTap{kq.p[cn], kEven, g}, QTap{qh.p[cn], rule_vel(cn), g}};
+            const TM mn{{QTap{kq.p[cn], kEven}, QTap{qh.p[cn], rule_vel(cn)}}};
             QNext<TM> n;
-            if (c < 2) n.fetch(mn, i0, j0, k0);
+            if (c < 2) n.fetch(mn, cells);
             qderiv<false>(L, F, t4);
-            if (c < 2) n.commit(L, mn);
+            if (c < 2) n.commit(L, mn, cells);
         }
         s += t4[3];
-        if (c == 2) s -= buoy;
         s += r0 * F.ml * adv.p[c][id];
         const double qnc = qn.p[c][id];
         const double tt = (-s / F.ml + r0 * qnc / P.dt) / (r0 / P.dt);
@@ -586,12 +596,13 @@ __global__ __launch_bounds__(QT) void pg_volume_fraction2_kernel(Grid g, const Q
 {
     __shared__ QLds L;
     const BCell X = bcell(g);
+    const QGeo cells = qgeo(g, X.i0, X.j0, X.k0);
     const size_t id = X.id;
     const int i = X.i, j = X.j, k = X.k;
     const double Kp = 300.0, Km = 300.0, beta = 0.1, eps_x = 1e-4, Kpos = 3.0, eps_k = 1e-7, h = g.h;
     const double kmin = 1e-4 / dt * h * h, kclamp = 0.05 / dt * h * h;
     double am[4];
-    qstage(L, QTap{advc, kEven, g}, X.i0, X.j0, X.k0);
+    qstage(L, QTap{advc, kEven}, cells);
     qderiv<false>(L, F, am);
     if (!X.valid) return;
     const double a = 2.0 * (am[3] / F.ml - advc[id]);
