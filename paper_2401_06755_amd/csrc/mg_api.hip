@@ -84,9 +84,9 @@ TileShape default_tiles(int nx, int ny, int nz, int zmul = 1)
 // 512; a last round of at most 256, one per compute unit, takes `single` times
 // as long per step as a full one.  A shorter chunk fills the chip better and
 // repeats the lead more often; a chunk that leaves a few workgroups for another
-// round costs that whole round.  Measured per step: two-sweep pass 3.2 us in a
-// full round, 2.1 us in a single one (FP64; FP32 2.4 and 1.8), residual 1.35
-// and 0.95 us.  zmul: the launches cover that many copies of the level.
+// round costs that whole round.  Measured per step: two-sweep pass 2.4 us in a
+// full round and 1.8 us in a single one in FP32, residual 1.35 and 0.95 us.
+// zmul: the launches cover that many copies of the level.
 TileShape march_tiles(int nx, int ny, int nz, int zmul, std::initializer_list<int> widths, int lead, double single)
 {
     TileShape best{};
@@ -116,10 +116,15 @@ TileShape march_tiles(int nx, int ny, int nz, int zmul, std::initializer_list<in
 // 64-wide residual tiles everywhere were slower: two-sweep pass and residual
 // at 96 x 64 x 160 (FP64) 38.7 and 18.5 us to 26.5 and 13.2 us, at 192 x 160 x
 // 224 (FP32) 90.7 and 43.7 us to 65 and 38 us.
+// single of the two-sweep pass: 0.8 (0.66 chose longer chunks on fewer workgroups;
+// 20 cycles at 112 x 80 x 160: FP64 1387 and, nodal, 1760 us to 1286 and 1656, FP32
+// nodal 1605 to 1454, at 80 x 48 x 112 1077 to 1056).  A group's launches cover 1 to
+// 16 copies, so its rounds are fuller than zmul says, and the longer chunks of
+// 0.66 serve it better: 40 served solves 43.7 ms, with 0.8 45.5.
 TileShape default_tiles_for(int nx, int ny, int nz, int kclass, bool fused, int zmul = 1)
 {
     if (kclass == NN4MG_KCLASS_FINE_RESID) return march_tiles(nx, ny, nz, zmul, {64, 32, 16}, 2, 0.7);
-    if (kclass == NN4MG_KCLASS_FINE_SWEEP_PROLONG && fused) return march_tiles(nx, ny, nz, zmul, {32, 16}, 4, 0.66);
+    if (kclass == NN4MG_KCLASS_FINE_SWEEP_PROLONG && fused) return march_tiles(nx, ny, nz, zmul, {32, 16}, 4, zmul > 1 ? 0.66 : 0.8);
     return default_tiles(nx, ny, nz, zmul);
 }
 
