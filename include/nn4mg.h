@@ -108,7 +108,8 @@ size_t nn4mg_bytes_required(const nn4mg_config *cfg);
  * Sec. 2.3.3).  Levels: halve while all dims are even and the smallest exceeds
  * cfg->min_coarse.  Coarse operators are the same filter at h_l = 2^l h with k
  * averaged over the 8 children.  The coarsest matrix (<= 512 unknowns) is
- * assembled, factorised and inverted on the host in FP64.
+ * assembled and inverted on the device in FP64; where the coarse end takes its
+ * dense form, that matrix (<= 1024 x 1024) is built here too.
  *   k_dev: nx*ny*nz device doubles, > 0, required iff coef_mode == NODAL; it
  *          is copied, so the caller may free it after the call returns.
  *   hip_stream: a hipStream_t (NULL = the null stream).
