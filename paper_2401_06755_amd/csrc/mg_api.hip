@@ -322,6 +322,15 @@ constexpr size_t kTailMaxCells = 1024;
 
 bool fcg_f32(const nn4mg_config *c) { return c->outer == NN4MG_OUTER_FCG && c->precision != NN4MG_PREC_FP64; }
 
+// Launch shape of the finest residual of cfg's hierarchy and of its
+// allocation-free form, whose norms agree to the last bit only in the same shape
+// (the sum follows the workgroups).
+TileShape fine_resid_tiles(const nn4mg_config *c, bool fused, int zmul = 1)
+{
+    if (fcg_f32(c)) return fcg_resid_tiles(c->nx, c->ny, c->nz);
+    return default_tiles_for(c->nx, c->ny, c->nz, NN4MG_KCLASS_FINE_RESID, fused, zmul);
+}
+
 // First level of the coarse end (0: none), and whether it takes the dense form
 // (dense_kernel).  Its one-workgroup kernel has to fit in FP64, which builds the
 // matrix.  Flexible CG around an FP32 cycle keeps the one-workgroup kernel: the
@@ -1036,7 +1045,7 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         const int zmul = group ? kGroupTileCopies : 1;
         for (int c = 0; c < 3; ++c)
             V.tiles[c] = default_tiles_for(V.nx, V.ny, V.nz, c, cfg->nu_post == 2 && H->L >= 2, zmul);
-        if (l == 0 && fcg_f32(cfg)) V.tiles[NN4MG_KCLASS_FINE_RESID] = fcg_resid_tiles(V.nx, V.ny, V.nz);
+        if (l == 0) V.tiles[NN4MG_KCLASS_FINE_RESID] = fine_resid_tiles(cfg, cfg->nu_post == 2 && H->L >= 2, zmul);
         if (V.tiles[0].blocks() > maxblk) maxblk = V.tiles[0].blocks();
         if (nodal) TRY(dalloc(H, &V.k, V.n));
         const bool single = (H->L == 1);
@@ -1207,7 +1216,7 @@ int nn4mg_residual_noalloc(const nn4mg_config *cfg, const double *k_dev, const d
     a.g.nz = cfg->nz;
     for (int f = 0; f < 6; ++f) a.g.bc[f] = cfg->bc[f];
     // the launch shape nn4mg_setup gives the finest residual of this config
-    a.t = default_tiles_for(cfg->nx, cfg->ny, cfg->nz, NN4MG_KCLASS_FINE_RESID, cfg->nu_post == 2 && L >= 2);
+    a.t = fine_resid_tiles(cfg, cfg->nu_post == 2 && L >= 2);
     a.h = cfg->h;
     a.omega = cfg->omega;
     a.yin = x_dev;
