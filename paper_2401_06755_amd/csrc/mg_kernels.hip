@@ -114,7 +114,15 @@ __global__ __launch_bounds__(512) void restrict_chain_kernel(const T *f, T *c1, 
         st = copy_ptr(st, off);
         partials = copy_ptr(partials, off);
     }
-    if (done && *done) return;
+    // The stopping workgroup may set the flag while the others of this launch run,
+    // so one thread reads it for the whole workgroup: waves reading it for
+    // themselves could disagree and part at the barriers below.
+    if (done) {
+        __shared__ int stop;
+        if (threadIdx.x == 0) stop = *done;
+        __syncthreads();
+        if (stop) return;
+    }
     if (st && g == 0) {
         // the extra first workgroup (dispatched first, so its reduction is off
         // the chain's critical path)
@@ -203,18 +211,23 @@ __global__ __launch_bounds__(512) void dense_kernel(const DenseArgs a)
         g -= c * a.nbc;
         off = (long long)c * a.bstride;
     }
+    __shared__ int stopped;
     const int *done = copy_ptr(a.done, off);
-    // the stopping flag is read with the first loads and tested before any write
+    const int n = a.n, t = threadIdx.x;
+    // The stopping flag is read with the first loads and tested before any write.
+    // The stopping workgroup may set it while the others of this launch run, so
+    // what the first wave read counts for the whole workgroup.
     const int stop = done ? *done : 0;
     if (a.st) {
         if (g == 0) {
-            if (!stop) stop_workgroup(copy_ptr(a.st, off), copy_ptr(a.partials, off), a.np);
+            if (t == 0) stopped = stop;
+            __syncthreads();
+            if (!stopped) stop_workgroup(copy_ptr(a.st, off), copy_ptr(a.partials, off), a.np);
             return;
         }
         g -= 1;
     }
     const double *m = copy_ptr(a.m, off);
-    const int n = a.n, t = threadIdx.x;
     const int il = t & (kDenseRows - 1), jg = t / kDenseRows, i = g * kDenseRows + il;
     const int ic = min(i, n - 1);
     double v[kDenseAhead];  // the first 512 columns, in flight with the right-hand side
@@ -237,8 +250,9 @@ __global__ __launch_bounds__(512) void dense_kernel(const DenseArgs a)
         const T *b = copy_ptr((const T *)a.b, off);
         for (int c = t; c < n; c += 512) sb[c] = (double)b[c];
     }
-    if (stop) return;  // uniform over the workgroup
+    if (t == 0) stopped = stop;
     __syncthreads();
+    if (stopped) return;
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
     for (int q = 0; q < kDenseAhead; q += 2) {
