@@ -11,6 +11,8 @@
 // is symmetric positive definite, so Gauss-Jordan elimination needs no
 // pivoting, and its pivots are the squares of the Cholesky factor's diagonal:
 // one that is not positive says that the matrix is not positive definite.
+// The inverse is symmetrised as it is stored: the cycle reads its columns as
+// rows, and flexible CG expects a symmetric preconditioner.
 //
 // A new coefficient replaces the inverse, so this is on the path of every time
 // step with a changing density.  Formed on the host (a copy of k out, Cholesky
@@ -163,6 +165,18 @@ __global__ __launch_bounds__(kNT1) void inverse_one_kernel(const CoarseArgs a)
             const int i = ty + 32 * r, j = tx + 32 * s;
             if (i < n && j < n) a.ainv[(size_t)i * n + j] = m[r][s];
         }
+    __syncthreads();
+    // symmetrised: each pair of entries by the thread of the upper one
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int s = 0; s < R; ++s) {
+            const int i = ty + 32 * r, j = tx + 32 * s;
+            if (i >= j || j >= n) continue;
+            const double v = 0.5 * (m[r][s] + a.ainv[(size_t)j * n + i]);
+            a.ainv[(size_t)i * n + j] = v;
+            a.ainv[(size_t)j * n + i] = v;
+        }
 }
 
 // n > 192: the matrix in memory, one workgroup per row.
@@ -283,19 +297,37 @@ __device__ __forceinline__ void invert_block(double (&m)[4], double (*buf)[2][kB
     if (bad && threadIdx.x == 0) flag[1] = 1;
 }
 
-// last = 1: only the block whose inverse is still to be put in place.
+// last = 1: the last diagonal block's inverse, and the whole inverse symmetrised
+// (the workgroup of an upper block averages it with the block across the diagonal).
 __global__ __launch_bounds__(kNTB) void trailing_kernel(const CoarseArgs a, int p, int last)
 {
     __shared__ double s0[kB][kB + 1], s1[kB][kB + 1], s2[kB][kB + 1];
     __shared__ double buf[2][2][kB];
     double m[4], u[4];
+    const int bi = blockIdx.y, bj = blockIdx.x;
     if (last) {
-        load_block(a, p, p, m);
-        invert_block(m, buf, a.flag);
-        store_block(a, p, p, m);
+        if (bi > bj) return;
+        load_block(a, bi, bj, m);
+        if (bi == p && bj == p) invert_block(m, buf, a.flag);
+        if (bi == bj)
+            to_lds(m, s1);
+        else {
+            load_block(a, bj, bi, u);
+            to_lds(u, s1);
+        }
+        __syncthreads();
+        const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[r] = 0.5 * (m[r] + s1[tx][ty + 8 * r]);
+        store_block(a, bi, bj, m);
+        if (bi == bj) return;
+        to_lds(m, s0);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) u[r] = s0[tx][ty + 8 * r];
+        store_block(a, bj, bi, u);
         return;
     }
-    const int bi = blockIdx.y, bj = blockIdx.x;
     if (bi == p || bj == p) return;
     load_block(a, bi, p, u);
     to_lds(u, s1);
@@ -371,7 +403,7 @@ hipError_t launch_coarse_inverse(const CoarseArgs &a, hipStream_t s)
         hipLaunchKernelGGL(trailing_kernel, dim3(nb, nb), dim3(kNTB), 0, s, a, p, 0);
         hipLaunchKernelGGL(panel_kernel, dim3(2 * nb), dim3(kNTB), 0, s, a, p, nb);
     }
-    hipLaunchKernelGGL(trailing_kernel, dim3(1), dim3(kNTB), 0, s, a, nb - 1, 1);
+    hipLaunchKernelGGL(trailing_kernel, dim3(nb, nb), dim3(kNTB), 0, s, a, nb - 1, 1);
     return hipGetLastError();
 }
 
