@@ -210,7 +210,9 @@ int nn4mg_get_tiles(nn4mg_t h, int level, int kclass, int *tx, int *ry, int *zc)
  * b_dev and x_dev as input (x_dev is overwritten), keep the fastest shape per
  * level and kernel class, and return them in tiles_out (9 ints per level: tx,
  * ry, zc for each of the 3 classes; (8, 8, 8) for the block form; may be
- * NULL).  Synchronous. */
+ * NULL).  The shapes on entry are candidates too, and stay unless whole cycles
+ * are faster in the others.  A new residual shape changes the last bits of the
+ * norms and of flexible CG's p . A p.  Synchronous. */
 int nn4mg_autotune(nn4mg_t h, const double *b_dev, double *x_dev, int *tiles_out, int max_levels);
 
 /* ---- Continuous-batching solve server ------------------------------------
