@@ -84,8 +84,9 @@ TileShape default_tiles(int nx, int ny, int nz, int zmul = 1)
 // 512; a last round of at most 256, one per compute unit, takes `single` times
 // as long per step as a full one.  A shorter chunk fills the chip better and
 // repeats the lead more often; a chunk that leaves a few workgroups for another
-// round costs that whole round.  Measured per step: two-sweep pass 2.4 us in a
-// full round and 1.8 us in a single one in FP32, residual 1.35 and 0.95 us.
+// round costs that whole round.  Measured per step at 256^3: two-sweep pass 2.4
+// us in a full round and 1.8 us in a single one in FP32, residual 1.35 and 0.95
+// us; what default_tiles_for passes as `single` is fitted to whole solves.
 // zmul: the launches cover that many copies of the level.
 TileShape march_tiles(int nx, int ny, int nz, int zmul, std::initializer_list<int> widths, int lead, double single)
 {
@@ -114,11 +115,12 @@ TileShape march_tiles(int nx, int ny, int nz, int zmul, std::initializer_list<in
 // the two-sweep pass in 64-wide tiles leaves one wave per SIMD).  A power-of-two
 // chunk that kept 512 workgroups, one row per thread with FP32 smoothing and
 // 64-wide residual tiles everywhere were slower: two-sweep pass and residual
-// at 96 x 64 x 160 (FP64) 38.7 and 18.5 us to 26.5 and 13.2 us, at 192 x 160 x
-// 224 (FP32) 90.7 and 43.7 us to 65 and 38 us.
-// single of the two-sweep pass: 0.8 (0.66 chose longer chunks on fewer workgroups;
-// 20 cycles at 112 x 80 x 160: FP64 1387 and, nodal, 1760 us to 1286 and 1656, FP32
-// nodal 1605 to 1454, at 80 x 48 x 112 1077 to 1056).  A group's launches cover 1 to
+// at 96 x 64 x 160 (FP64) 38.7 and 18.5 us, here 25.4 and 13.0 us; at 192 x 160 x
+// 224 (FP32) 90.7 and 43.7 us, here 55 and 37 us (nodal, HIP events).
+// single of the two-sweep pass: 0.8, fitted to solves rather than the 0.75 of the
+// steps above (0.66 chose longer chunks on fewer workgroups; 20 cycles at 112 x 80
+// x 160: FP64 1387 and, nodal, 1760 us to 1286 and 1656, FP32 nodal 1605 to 1454,
+// at 80 x 48 x 112 1077 to 1056).  A group's launches cover 1 to
 // 16 copies, so its rounds are fuller than zmul says, and the longer chunks of
 // 0.66 serve it better: 40 served solves 43.7 ms, with 0.8 45.5.
 TileShape default_tiles_for(int nx, int ny, int nz, int kclass, bool fused, int zmul = 1)
@@ -651,9 +653,11 @@ int enqueue_sweep2(nn4mg_hier *H, int l, const void *b, void *y, double *x64, in
 
 // Largest level that defaults to the block form of the two sweeps: its time
 // grows with the cells from the start, that of a march over z with its chain of
-// plane steps.  Blocks and best march, us: 32^3 FP64 nodal 8.8 and 14.5, 48^3
-// 13.8 and 16.6, 64^3 17.0 and 16.1 (constant 14.3 and 14.8, FP32 9.5 and 12.1),
-// 64 x 64 x 128 27.4 and 20.2.  Over several copies the cells count together (as in
+// plane steps.  A cycle with blocks on the finest level and with the march that
+// the default rule would take, us: 48^3 FP64 nodal 35.4 and 39.0, 64^3 39.9 and
+// 41.0 (39.6 with one-row tiles, which only the autotuner tries), FP64 constant
+// 33.2 and 36.6, FP32 constant 29.3 and 32.5, nodal 34.9 and 37.9.  Beyond, the
+// march: 64 x 64 x 128 FP64 nodal 20.2 us a pass, in blocks 27.4.  Over several copies the cells count together (as in
 // kGroupTileCopies): 8 copies of a 64^3 level in FP32 took 47 us in blocks, while
 // a march over as many cells takes 27.
 constexpr size_t kBlock2MaxCells = 64 * 64 * 64;

@@ -17,9 +17,9 @@
 // A new coefficient replaces the inverse, so this is on the path of every time
 // step with a changing density.  Formed on the host (a copy of k out, Cholesky
 // and n triangular solves on one core, a copy back) a coefficient update plus
-// 20 cycles at 96 x 64 x 160 (n = 240) took 9.56 ms; here it takes 2.57 ms.
-// The served stream, whose worker formed one inverse per request, gained a
-// tenth (40 solves of 32^3 .. 128^3: 59.7 to 54.0 ms).
+// 20 cycles at 96 x 64 x 160 (n = 240) took 9.56 ms, and with the inverse formed
+// here and nothing else changed 2.57 ms (now 1.88).  40 served solves of 32^3 ..
+// 128^3, whose worker formed one inverse per request: 59.7 and 54.0 ms (now 44.5).
 #include "mg_internal.h"
 
 namespace nn4mg {

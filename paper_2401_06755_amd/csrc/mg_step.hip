@@ -677,11 +677,12 @@ int hip_fail(hipError_t e, const char *what)
     } while (0)
 
 dim3 cells_grid(const Grid &g) { return dim3((unsigned)((g.n + 255) / 256)); }
-// Fixed-cycle solve of A x = b on the pressure hierarchy; the work pair
-// (b, px) is the same for every solve, so a captured cycle stays valid.  The
-// solve is enqueued with nothing waited for on the host (its status, residual
-// and time are read by collect_solves after the step); hierarchies that need
-// the host inside the solve (singular ones) take the synchronous solve.
+
+// Fixed-cycle solve of A x = b on the pressure hierarchy; the work pair (b, px)
+// is the same for every solve.  The solve is enqueued with nothing waited for on
+// the host (its status, residual and time are read by collect_solves after the
+// step); hierarchies that need the host inside the solve (singular ones) take
+// the synchronous solve.
 int pressure_solve(nn4mg_stepper *S, int slot, int cycles, nn4mg_step_info *info, float *ms_mg)
 {
     STEP_TRY(hipEventRecord(S->sev[2 * slot], S->s), "hipEventRecord");
