@@ -120,9 +120,9 @@ TileShape march_tiles(int nx, int ny, int nz, int zmul, std::initializer_list<in
 // single of the two-sweep pass: 0.8, fitted to solves rather than the 0.75 of the
 // steps above (0.66 chose longer chunks on fewer workgroups; 20 cycles at 112 x 80
 // x 160: FP64 1387 and, nodal, 1760 us to 1286 and 1656, FP32 nodal 1605 to 1454,
-// at 80 x 48 x 112 1077 to 1056).  A group's launches cover 1 to
-// 16 copies, so its rounds are fuller than zmul says, and the longer chunks of
-// 0.66 serve it better: 40 served solves 43.7 ms, with 0.8 45.5.
+// at 80 x 48 x 112 1077 to 1056).  Launches of a group over several copies (zmul:
+// at most four) have fuller rounds than zmul says where more run, and the longer
+// chunks of 0.66 serve them better: 40 served solves 43.7 ms, with 0.8 45.5.
 TileShape default_tiles_for(int nx, int ny, int nz, int kclass, bool fused, int zmul = 1)
 {
     if (kclass == NN4MG_KCLASS_FINE_RESID) return march_tiles(nx, ny, nz, zmul, {64, 32, 16}, 2, 0.7);
@@ -258,7 +258,8 @@ struct nn4mg_hier {
 namespace {
 
 constexpr size_t kArenaAlign = 256;
-// Running copies a group's default launch shapes are chosen for.
+// Running copies a group's residual shape is chosen for, and at most its sweeps'
+// (group_sweep_shapes).
 constexpr int kGroupTileCopies = 4;
 
 size_t arena_round(size_t v) { return (v + kArenaAlign - 1) & ~(kArenaAlign - 1); }
@@ -657,9 +658,9 @@ int enqueue_sweep2(nn4mg_hier *H, int l, const void *b, void *y, double *x64, in
 // the default rule would take, us: 48^3 FP64 nodal 35.4 and 39.0, 64^3 39.9 and
 // 41.0 (39.6 with one-row tiles, which only the autotuner tries), FP64 constant
 // 33.2 and 36.6, FP32 constant 29.3 and 32.5, nodal 34.9 and 37.9.  Beyond, the
-// march: 64 x 64 x 128 FP64 nodal 20.2 us a pass, in blocks 27.4.  Over several copies the cells count together (as in
-// kGroupTileCopies): 8 copies of a 64^3 level in FP32 took 47 us in blocks, while
-// a march over as many cells takes 27.
+// march: 64 x 64 x 128 FP64 nodal 20.2 us a pass, in blocks 27.4.  Over several
+// copies the cells count together: 8 copies of a 64^3 level in FP32 took 47 us in
+// blocks, while a march over as many cells takes 27.
 constexpr size_t kBlock2MaxCells = 64 * 64 * 64;
 
 bool level_fusable(const nn4mg_hier *H, int l)
@@ -1043,9 +1044,9 @@ int nn4mg::setup_hier(const nn4mg_config *cfg, const double *k_dev, hipStream_t 
         V.nz = cfg->nz >> l;
         V.h = cfg->h * (double)(1 << l);
         V.n = (size_t)V.nx * V.ny * V.nz;
-        // a group's launches usually cover several running copies (the same
-        // shapes whatever the group's size, so a request's result does not
-        // depend on the group it runs in)
+        // a group's launches usually cover several running copies; the residual's
+        // shape is the same whatever their number and the group's size, since its
+        // norm follows it and a request's result must not depend on either
         const int zmul = group ? kGroupTileCopies : 1;
         for (int c = 0; c < 3; ++c)
             V.tiles[c] = default_tiles_for(V.nx, V.ny, V.nz, c, cfg->nu_post == 2 && H->L >= 2, zmul);
@@ -1631,10 +1632,29 @@ int hier_load_coef(nn4mg_hier *H, const double *k_dev)
     return set_coef(H, nullptr);
 }
 
+// Shapes of a group's two-sweep passes for launches over k copies (captured per
+// k): any shape and either form gives the same bits, so they may follow the
+// launch, unlike the residual's.  One running copy in the shapes for four marches
+// its chunks on a quarter of the workgroups: a request alone, in those shapes and
+// in these, 64^3 FP64 3.12 and 2.65 ms, 96^3 6.80 and 5.28, 128^3 11.25 and 7.83;
+// FP32 2.88 and 2.48, 6.00 and 4.61, 9.51 and 6.87.
+void group_sweep_shapes(nn4mg_hier *G, int k)
+{
+    const int copies = std::min(k, kGroupTileCopies);
+    for (int l = 0; l < G->L; ++l) {
+        Level &V = G->lv[l];
+        if (!level_fusable(G, l)) continue;
+        V.tiles[NN4MG_KCLASS_FINE_SWEEP_PROLONG] =
+            default_tiles_for(V.nx, V.ny, V.nz, NN4MG_KCLASS_FINE_SWEEP_PROLONG, true, copies);
+        V.block2 = V.n * copies <= kBlock2MaxCells;
+    }
+}
+
 // The batched cycle over copies 0 .. k - 1, captured once per k.
 hipGraphExec_t batch_graph(nn4mg_hier *G, int k)
 {
     if (G->bgraph[k]) return G->bgraph[k];
+    group_sweep_shapes(G, k);
     if (!G->graphs_ok || G->prof_on) return nullptr;
     hipGraph_t g = nullptr;
     if (hipStreamBeginCapture(G->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
