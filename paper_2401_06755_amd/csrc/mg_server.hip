@@ -141,17 +141,24 @@ size_t request_bytes(const nn4mg_config &cfg, bool dense)
 }
 
 // Whether requests of cfg run with the coarse end as a matrix (8 n^2 bytes per
-// copy, up to 8 MiB): only where the budget holds a full group that way, so a
-// small budget admits what it admits without.  Fixed for a server and a
-// configuration, so results do not depend on the load.  A budget that several
-// configurations fill still gains, although the matrices leave room for fewer
-// copies: 512 solves of 32^3 to 128^3 under 1 GiB 515-554 a second before there
-// were matrices, now 565-595; under 0.25 GiB 438-483 and 486-506; six
-// configurations of 32^3 under 64 MiB 1390-1520 and 1705-2095.
+// copy, up to 8 MiB).  A group's launches are shared by its copies, so the
+// matrix gains a few per cent there and is not worth a copy that would not fit:
+// only where a full group that way takes an eighth of the budget at most, or
+// where the matrix is a 32nd of the copy and the budget holds a full group.
+// Fixed for a server and a configuration, so results do not depend on the load.
+// Solves a second without matrices, with them wherever the budget held one full
+// group, and by this rule: 32^3 to 96^3 in FP64 under 256 MiB 798, 780 and 954,
+// under 512 MiB 880, 1112 and 1208, under 1 GiB 911, 1244 and 1257 (the first of
+// each an earlier build); the same in FP32 under 64 MiB 440, 378 and 427-450; six
+// configurations of 32^3 under 64 MiB 1461, 1764 and 2440.  A quarter of the
+// budget, or a matrix of an eighth of the copy, still lost in places (256 MiB in
+// FP32 854, 384 MiB 1041, where this rule gives 990 and 1190).
 bool dense_requests(const nn4mg_server *S, const nn4mg_config &cfg)
 {
     const int cap = S->max_active < kGroupCap ? S->max_active : kGroupCap;
-    return (size_t)cap * request_bytes(cfg, true) <= S->budget;
+    const size_t with = request_bytes(cfg, true), without = request_bytes(cfg, false);
+    const size_t group = (size_t)cap * with;
+    return group <= S->budget / 8 || (group <= S->budget && with - without <= without / 32);
 }
 
 void push_result(nn4mg_server *S, const Request &q, double t_start, const nn4mg_info &info, int status,
