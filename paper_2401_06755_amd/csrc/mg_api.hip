@@ -120,9 +120,8 @@ TileShape march_tiles(int nx, int ny, int nz, int zmul, std::initializer_list<in
 // single of the two-sweep pass: 0.8, fitted to solves rather than the 0.75 of the
 // steps above (0.66 chose longer chunks on fewer workgroups; 20 cycles at 112 x 80
 // x 160: FP64 1387 and, nodal, 1760 us to 1286 and 1656, FP32 nodal 1605 to 1454,
-// at 80 x 48 x 112 1077 to 1056).  Launches of a group over several copies (zmul:
-// at most four) have fuller rounds than zmul says where more run, and the longer
-// chunks of 0.66 serve them better: 40 served solves 43.7 ms, with 0.8 45.5.
+// at 80 x 48 x 112 1077 to 1056).  Launches over several copies of a group: 0.66,
+// whose longer chunks served better (40 served solves 43.7 ms, with 0.8 45.5).
 TileShape default_tiles_for(int nx, int ny, int nz, int kclass, bool fused, int zmul = 1)
 {
     if (kclass == NN4MG_KCLASS_FINE_RESID) return march_tiles(nx, ny, nz, zmul, {64, 32, 16}, 2, 0.7);
@@ -258,8 +257,7 @@ struct nn4mg_hier {
 namespace {
 
 constexpr size_t kArenaAlign = 256;
-// Running copies a group's residual shape is chosen for, and at most its sweeps'
-// (group_sweep_shapes).
+// Running copies a group's residual shape is chosen for.
 constexpr int kGroupTileCopies = 4;
 
 size_t arena_round(size_t v) { return (v + kArenaAlign - 1) & ~(kArenaAlign - 1); }
@@ -1637,16 +1635,17 @@ int hier_load_coef(nn4mg_hier *H, const double *k_dev)
 // launch, unlike the residual's.  One running copy in the shapes for four marches
 // its chunks on a quarter of the workgroups: a request alone, in those shapes and
 // in these, 64^3 FP64 3.12 and 2.65 ms, 96^3 6.80 and 5.28, 128^3 11.25 and 7.83;
-// FP32 2.88 and 2.48, 6.00 and 4.61, 9.51 and 6.87.
+// FP32 2.88 and 2.48, 6.00 and 4.61, 9.51 and 6.87.  Beyond four likewise: 48
+// solves of 128^3 FP32, six running, 290 a second in the shapes for four and 293,
+// up to sixteen running 397 and 415.
 void group_sweep_shapes(nn4mg_hier *G, int k)
 {
-    const int copies = std::min(k, kGroupTileCopies);
     for (int l = 0; l < G->L; ++l) {
         Level &V = G->lv[l];
         if (!level_fusable(G, l)) continue;
         V.tiles[NN4MG_KCLASS_FINE_SWEEP_PROLONG] =
-            default_tiles_for(V.nx, V.ny, V.nz, NN4MG_KCLASS_FINE_SWEEP_PROLONG, true, copies);
-        V.block2 = V.n * copies <= kBlock2MaxCells;
+            default_tiles_for(V.nx, V.ny, V.nz, NN4MG_KCLASS_FINE_SWEEP_PROLONG, true, k);
+        V.block2 = V.n * k <= kBlock2MaxCells;
     }
 }
 
