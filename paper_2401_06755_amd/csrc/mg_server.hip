@@ -566,18 +566,24 @@ bool poll_group(nn4mg_server *S, Group *g)
 // cycles as the member closest to its end has planned (members that have not
 // run a batch yet have no estimate and do not shorten it), over the copies up
 // to the last running one, then every running member's state header, then the
-// group's event.
+// group's event.  A group whose members have all yet to start waits for those
+// whose set-up is in flight: their first batch has kMaxBatchCycles cycles, and
+// one that the first to arrive began alone would keep the others out of it.
 bool launch_group(nn4mg_server *S, Group *g)
 {
     if (g->in_flight) return false;
     int n = kMaxBatchCycles, k = 0;
+    bool started = false, joining = false;
     for (size_t i = 0; i < g->m.size(); ++i) {
         const Member &mb = g->m[i];
+        joining = joining || mb.state == M_ADMIT;
         if (mb.state != M_RUNNING) continue;
         k = (int)i + 1;
-        if (hier_started(mb.V) && hier_planned(mb.V) < n) n = hier_planned(mb.V);
+        if (!hier_started(mb.V)) continue;
+        started = true;
+        if (hier_planned(mb.V) < n) n = hier_planned(mb.V);
     }
-    if (k == 0) return false;
+    if (k == 0 || (joining && !started)) return false;
     if (n < 1) n = 1;
     int rc = batch_enqueue_cycles(g->G, n, k);
     for (Member &mb : g->m) {
