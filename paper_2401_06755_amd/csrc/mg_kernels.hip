@@ -220,9 +220,9 @@ __global__ __launch_bounds__(512) void dense_kernel(const DenseArgs a)
     const int stop = done ? *done : 0;
     if (a.st) {
         if (g == 0) {
-            if (t == 0) stopped = stop;
-            __syncthreads();
-            if (!stopped) stop_workgroup(copy_ptr(a.st, off), copy_ptr(a.partials, off), a.np);
+            // (it sets the flag itself, behind a barrier that each wave reaches
+            // with the flag read)
+            if (!stop) stop_workgroup(copy_ptr(a.st, off), copy_ptr(a.partials, off), a.np);
             return;
         }
         g -= 1;
